@@ -250,7 +250,12 @@ def test_gemm_lm_head_large_window_sampled():
 
 
 @pytest.mark.parametrize("M,N,K,epi", [(3, 50, 70, nb.NJ_GEMM_STORE), (8, 768, 256, nb.NJ_GEMM_RESIDUAL),
-                                       (8, 2 * 688, 256, nb.NJ_GEMM_SWIGLU)])
+                                       (8, 2 * 688, 256, nb.NJ_GEMM_SWIGLU),
+                                       # rows per wave 2, 4, 8 and their remainders; K below, at and past a load group
+                                       (1, 7, 1, nb.NJ_GEMM_STORE), (2, 64, 255, nb.NJ_GEMM_RESIDUAL),
+                                       (4, 33, 256, nb.NJ_GEMM_STORE), (5, 2 * 21, 257, nb.NJ_GEMM_SWIGLU),
+                                       (9, 129, 688, nb.NJ_GEMM_RESIDUAL), (23, 40, 1000, nb.NJ_GEMM_STORE),
+                                       (8200, 4, 32, nb.NJ_GEMM_STORE)])  # more row blocks than grid rows
 def test_gemm_f32(M, N, K, epi):
     rng = np.random.default_rng(3)
     x = rng.standard_normal((M, K), dtype=np.float32)
@@ -317,6 +322,30 @@ def test_accept_matches_oracle(B, k, V, std, beta):
     assert not res["mismatches"], res["mismatches"][:5]
     assert res["checked"] >= B // 2
     assert np.all((acc >= 0) & (acc <= k))
+
+
+@pytest.mark.parametrize("V", [16, 20, 100, 128, 132, 1004, 4112, 4099])
+def test_accept_unaligned_logits_give_the_same_bits(V):
+    """The statistics read 16-byte pieces where rows are aligned and single
+    entries elsewhere (ragged ends, a base that is only 4-byte aligned, V not a
+    multiple of 4): the same entries in the same order, so the same outputs."""
+    B, k = 5, 2
+    logits, drafts, q, u = _accept_case(B, k, V, 7 + V, 1.5, 0.5)
+    acc, nxt = _run_accept(V, logits, drafts, q, u)
+    assert not compare(acc, nxt, logits, drafts, q, u)["mismatches"]
+    desc = model_desc(dataclasses.replace(W.TINY_F32, vocab=V))
+    nbytes = nb.accept_workspace_bytes(V, B, k)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    nb.workspace_init(ws.data_ptr(), nbytes, _stream())
+    flat = torch.zeros(logits.size + 1, dtype=torch.float32, device="cuda")
+    flat[1:] = _dev(logits).view(-1)
+    dd, dq, du = _dev(drafts), _dev(q), _dev(u)
+    acc2 = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+    nxt2 = torch.full((B, k + 1), -7, dtype=torch.int32, device="cuda")
+    nb.accept(desc, flat[1:].data_ptr(), dd.data_ptr(), dq.data_ptr(), du.data_ptr(), B, k, acc2.data_ptr(),
+              nxt2.data_ptr(), ws.data_ptr(), nbytes, _stream())
+    torch.cuda.synchronize()
+    assert np.array_equal(acc2.cpu().numpy(), acc) and np.array_equal(nxt2.cpu().numpy(), nxt)
 
 
 def test_accept_identical_draft_accepts_everything():
