@@ -5,19 +5,21 @@
 // bf16 path.  One workgroup (4 waves) per (sequence, KV head, KV split).  The
 // G query heads sharing a KV head and the T = k+1 window positions are packed
 // into R = T*G query rows (at most 64 = 4 tiles of 16), so every key and value
-// byte read from HBM serves all of them.  Per 16-token block a wave computes
-//   S^T (16 tokens x 16 rows) = K . Q^T      with 4 x mfma 16x16x32 bf16
-// which leaves lane l holding tokens 4*(l>>4)+i of query row l&15 -- exactly
-// the B operand of
-//   O^T (16 dims x 16 rows) += V^T . P^T     with mfma 16x16x16 bf16,
+// byte read from HBM serves all of them.  Blocks are taken in pairs of 32
+// tokens: a wave computes
+//   S^T (32 tokens x 16 rows) = K . Q^T      with 8 x mfma 16x16x32 bf16,
+// the tokens dealt to the MFMAs' rows so that each lane ends up with eight
+// consecutive tokens of one query row -- exactly the B operand of
+//   O^T (16 dims x 16 rows) += V^T . P^T     with mfma 16x16x32 bf16,
 // so the softmax numerators go straight from the score registers into the
-// second product with no data exchange.  The A operand V^T needs 4
-// consecutive tokens of one dim: V pages are stored dim-major inside a block
-// ([D][16]), which makes that an 8-byte read.  Softmax is online in the log2
+// second product with no data exchange.  The A operand V^T needs the same
+// eight tokens of one dim: V pages are stored dim-major inside a block
+// ([D][16]), which makes that one 16-byte read.  Softmax is online in the log2
 // domain.  When the grid splits the KV range, each split writes its partial
 // (o, max, sum) and the last split to arrive merges them in split order.
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "attn_work.h"
 #include "common.h"
@@ -27,16 +29,7 @@ namespace nj {
 namespace {
 
 constexpr int kD = 128;  // head dim of the bf16 path
-#ifndef NJ_ATTN_BUF
-#define NJ_ATTN_BUF 2
-#endif
-#ifndef NJ_ATTN_CHUNK
-#define NJ_ATTN_CHUNK 4
-#endif
-constexpr int kAttnBuf = NJ_ATTN_BUF;      // chunk buffers per workgroup (kAttnBuf - 1 chunks in flight)
-constexpr int kAttnChunk = NJ_ATTN_CHUNK;  // cached blocks per chunk
-// workgroups per CU that the chunk buffers leave room for (160 KB of LDS)
-constexpr int attn_wgs_per_cu(int nbuf, int cb) { return (160 * 1024 - 1024) / (nbuf * cb * 8 * 1024); }
+constexpr int kAttnWgsPerCu = 2;  // resident attention workgroups per CU (registers, LDS of the larger forms)
 
 __device__ __forceinline__ bf16x8 ld8(const bf16_t* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p));
@@ -68,35 +61,18 @@ __device__ __forceinline__ u32x2* out_at(const AttnK& a, int m, int c) {
                                          : a.out + (size_t)m * a.H * kD + c);
 }
 
-// The workgroup
-// streams its KV range in chunks of kCB blocks, loaded straight into LDS
-// while earlier ones are multiplied out of LDS (NBUF buffers, NBUF-1 chunks in
-// flight).  Waves are split into
-// RTW row tiles x (4 / RTW) token phases: a wave multiplies its row tile
-// against every (4/RTW)-th block of the chunk, and the phases of a tile are
-// merged at the end.  LDS rows are XOR-swizzled in 16-byte (K) and 8-byte (V)
-// units so that the fragment reads of 16 consecutive rows hit distinct banks.
-constexpr int kKPieces = kBlock * kD / 8;  // 16-byte pieces per K (or V) block: 256
-
-__device__ __forceinline__ int k_lds(int tok, int chunk16) {  // element offset in a K block [16][128]
-  return tok * kD + ((chunk16 ^ tok) & 15) * 8;
-}
-__device__ __forceinline__ int v_lds(int dim, int unit8) {  // element offset in a V block [128][16]
-  return dim * kBlock + ((unit8 ^ (((dim >> 3) & 1) << 1)) & 3) * 4;
-}
-
 // A split has written its partial (o, max, sum) with device-coherent stores;
 // count it in, and let the last split of the (sequence, KV head) to arrive
 // merge all splits in split order:
 //   out = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s.
-// The per-split (m, l) of every query row go to LDS first and each row's
-// weights 2^(m_s - M) are formed once; then each thread merges 4 head dims of
-// one query row per unit, with the loads of all splits of a unit in flight
-// together.  `lds` is the kernel's staging buffer (free by now).
-constexpr int kMergeSplits = 8;   // split partials loaded together per unit
-constexpr int kMergeUnits = 4;    // units merged together per thread
+// A thread merges up to kMergeUnits units of 4 head dims of one query row; the
+// (m, l) and o of kMergeSplits splits of all its units are loaded together
+// (one memory round trip; reading every (m, l) first cost a second one), and
+// more splits than that fold in with a running max.
+constexpr int kMergeSplits = 4;
+constexpr int kMergeUnits = 4;
 __device__ void split_arrive(const AttnK& a, int pair, int nsplit, int slot0, int R, int RT, int G, int b, int kvh,
-                             __amdgpu_buffer_rsrc_t ors, __amdgpu_buffer_rsrc_t mrs, float* lds, int lds_floats) {
+                             __amdgpu_buffer_rsrc_t ors, __amdgpu_buffer_rsrc_t mrs) {
   __shared__ int s_last;
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -106,406 +82,546 @@ __device__ void split_arrive(const AttnK& a, int pair, int nsplit, int slot0, in
   if (!s_last) return;
   const int rpad = RT * 16;
   const size_t pbase = (size_t)slot0 * rpad;
-  // s_f[qr][sp]: weight 2^(m_sp - M) of split sp for row qr (0 for empty
-  // splits); s_w[qr]: 1 / sum_sp weight * l_sp.  The (m, l) of every row and
-  // split are loaded in one pass.
-  float* s_f = lds;
-  float* s_l = lds + R * nsplit;
-  float* s_w = lds + 2 * R * nsplit;
-  if (2 * R * nsplit + R <= lds_floats) {
-    for (int u = threadIdx.x; u < R * nsplit; u += 256) {
-      const int qr = u / nsplit, sp = u % nsplit;
-      const uint32_t off = (uint32_t)(((pbase + (size_t)sp * rpad + qr) * 2) * 4);
-      s_f[u] = coherent_load_f32(mrs, off);
-      s_l[u] = coherent_load_f32(mrs, off + 4);
+  const int nunits = R * (kD / 4);
+  for (int ub = 0; ub < nunits; ub += 256 * kMergeUnits) {
+    f32x4 acc[kMergeUnits];
+    float mx[kMergeUnits], wsum[kMergeUnits];
+#pragma unroll
+    for (int q = 0; q < kMergeUnits; ++q) {
+      acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      mx[q] = -INFINITY;
+      wsum[q] = 0.f;
     }
-    __syncthreads();
-    for (int qr = threadIdx.x; qr < R; qr += 256) {
-      float mx = -INFINITY;
-      for (int sp = 0; sp < nsplit; ++sp) mx = fmaxf(mx, s_f[qr * nsplit + sp]);
-      // an empty split wrote only its -inf marker: its l and o slots hold
-      // whatever the workspace held before, so it is masked out, not weighted 0
-      float wsum = 0.f;
-      for (int sp = 0; sp < nsplit; ++sp) {
-        const float m = s_f[qr * nsplit + sp];
-        const float f = (m == -INFINITY) ? 0.f : exp2f(m - mx);
-        s_f[qr * nsplit + sp] = f;
-        if (m != -INFINITY) wsum += f * s_l[qr * nsplit + sp];
-      }
-      s_w[qr] = 1.0f / wsum;
-    }
-    __syncthreads();
-    // each unit: 4 head dims of one row.  A thread takes up to kMergeUnits
-    // units at a time and issues the loads of all their splits (kMergeSplits
-    // at a time) together.
-    const int nunits = R * (kD / 4);
-    for (int ub = 0; ub < nunits; ub += 256 * kMergeUnits) {
-      f32x4 acc[kMergeUnits];
+    for (int s0 = 0; s0 < nsplit; s0 += kMergeSplits) {
+      f32x4 ov[kMergeUnits][kMergeSplits];
+      float2 ml[kMergeUnits][kMergeSplits];
 #pragma unroll
-      for (int q = 0; q < kMergeUnits; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int s0 = 0; s0 < nsplit; s0 += kMergeSplits) {
-        f32x4 ov[kMergeUnits][kMergeSplits];
+      for (int q = 0; q < kMergeUnits; ++q) {
+        if (ub + q * 256 >= nunits) break;  // uniform
+        const int u = min(ub + (int)threadIdx.x + q * 256, nunits - 1);
+        const int qr = u / (kD / 4), d = (u % (kD / 4)) * 4;
 #pragma unroll
-        for (int q = 0; q < kMergeUnits; ++q) {
-          const int u = min(ub + (int)threadIdx.x + q * 256, nunits - 1);
-          const int qr = u / (kD / 4), d = (u % (kD / 4)) * 4;
-#pragma unroll
-          for (int j = 0; j < kMergeSplits; ++j) {
-            const int sp = min(s0 + j, nsplit - 1);
-            ov[q][j] = coherent_load(ors, (uint32_t)(((pbase + (size_t)sp * rpad + qr) * kD + d) * 4));
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < kMergeUnits; ++q) {
-          const int qr = min(ub + (int)threadIdx.x + q * 256, nunits - 1) / (kD / 4);
-#pragma unroll
-          for (int j = 0; j < kMergeSplits; ++j)
-            if (s0 + j < nsplit && s_f[qr * nsplit + s0 + j] != 0.f) acc[q] += s_f[qr * nsplit + s0 + j] * ov[q][j];
+        for (int j = 0; j < kMergeSplits; ++j) {
+          const size_t row = pbase + (size_t)min(s0 + j, nsplit - 1) * rpad + qr;
+          ml[q][j] = coherent_load_f32x2(mrs, (uint32_t)(row * 8));
+          ov[q][j] = coherent_load(ors, (uint32_t)((row * kD + d) * 4));
         }
       }
 #pragma unroll
       for (int q = 0; q < kMergeUnits; ++q) {
-        const int u = ub + (int)threadIdx.x + q * 256;
-        if (u >= nunits) break;
-        const int qr = u / (kD / 4), d = (u % (kD / 4)) * 4;
-        const float inv = s_w[qr];
-        const int i = qr / G, hh = qr % G;
-        u32x2 o;
-        o[0] = pack_bf16x2(acc[q][0] * inv, acc[q][1] * inv);
-        o[1] = pack_bf16x2(acc[q][2] * inv, acc[q][3] * inv);
-        *out_at(a, b * a.T + i, (kvh * G + hh) * kD + d) = o;
+        if (ub + q * 256 >= nunits) break;
+        float bm = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < kMergeSplits; ++j)
+          if (s0 + j < nsplit) bm = fmaxf(bm, ml[q][j].x);
+        const float mn = fmaxf(mx[q], bm);
+        if (mn == -INFINITY) continue;  // only empty splits so far
+        const float alpha = mx[q] == -INFINITY ? 0.f : exp2f(mx[q] - mn);
+        acc[q] *= alpha;
+        wsum[q] *= alpha;
+        mx[q] = mn;
+        // an empty split wrote only its -inf marker: its l and o slots hold
+        // whatever the workspace held before, so it is skipped, not weighted 0
+#pragma unroll
+        for (int j = 0; j < kMergeSplits; ++j)
+          if (s0 + j < nsplit && ml[q][j].x != -INFINITY) {
+            const float f = exp2f(ml[q][j].x - mn);
+            wsum[q] += f * ml[q][j].y;
+            acc[q] += f * ov[q][j];
+          }
       }
     }
-    return;
-  }
-  // too many splits to stage (not reached by attention_plan's splits): direct loads
-  for (int u = threadIdx.x; u < R * (kD / 4); u += 256) {
-    const int qr = u / (kD / 4), d = (u % (kD / 4)) * 4;
-    float mx = -INFINITY;
-    for (int sp = 0; sp < nsplit; ++sp)
-      mx = fmaxf(mx, coherent_load_f32(mrs, (uint32_t)(((pbase + (size_t)sp * rpad + qr) * 2) * 4)));
-    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    float wsum = 0.f;
-    for (int sp = 0; sp < nsplit; ++sp) {
-      const size_t base = pbase + (size_t)sp * rpad + qr;
-      const float m = coherent_load_f32(mrs, (uint32_t)((base * 2) * 4));
-      if (m == -INFINITY) continue;  // empty split: only its marker was written
-      const float f = exp2f(m - mx);
-      wsum += f * coherent_load_f32(mrs, (uint32_t)((base * 2 + 1) * 4));
-      acc += f * coherent_load(ors, (uint32_t)((base * kD + d) * 4));
+#pragma unroll
+    for (int q = 0; q < kMergeUnits; ++q) {
+      const int u = ub + (int)threadIdx.x + q * 256;
+      if (u >= nunits) break;
+      const int qr = u / (kD / 4), d = (u % (kD / 4)) * 4;
+      const float inv = 1.0f / wsum[q];
+      const int i = qr / G, hh = qr % G;
+      u32x2 o;
+      o[0] = pack_bf16x2(acc[q][0] * inv, acc[q][1] * inv);
+      o[1] = pack_bf16x2(acc[q][2] * inv, acc[q][3] * inv);
+      *out_at(a, b * a.T + i, (kvh * G + hh) * kD + d) = o;
     }
-    const float inv = 1.0f / wsum;
-    const int i = qr / G, hh = qr % G;
-    u32x2 o;
-    o[0] = pack_bf16x2(acc[0] * inv, acc[1] * inv);
-    o[1] = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-    *out_at(a, b * a.T + i, (kvh * G + hh) * kD + d) = o;
   }
 }
 
-template <int RTW, int NBUF, int kCB>
-__global__ __launch_bounds__(256, attn_wgs_per_cu(NBUF, kCB)) void attn_lds_kernel(AttnK a) {
-  constexpr int NTP = 4 / RTW;  // token phases per row tile
-  constexpr int KV_ELEMS = kCB * kBlock * kD;  // one chunk of K (or V)
-  constexpr int WPB = 4 / kCB;  // waves loading one block (its K and V halves when 2)
-  constexpr int UPW = 8 / WPB;  // 1 KB load instructions per wave and chunk
-  static_assert(kCB == 2 || kCB == 4, "a chunk's blocks split evenly over the 4 waves");
-  __shared__ __attribute__((aligned(16))) bf16_t smem[NBUF * 2 * KV_ELEMS];  // [buf][K|V][chunk], 32 KB per buffer
+// Max over the lanes that share lane % 16 (a query row's four lanes).
+__device__ __forceinline__ float row_max(float v) {
+  const uint32_t x = __float_as_uint(v);
+  const auto p16 = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  const float m = fmaxf(__uint_as_float(p16[0]), __uint_as_float(p16[1]));
+  const uint32_t y = __float_as_uint(m);
+  const auto p32 = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+  return fmaxf(__uint_as_float(p32[0]), __uint_as_float(p32[1]));
+}
+
+// One online-softmax step of a query row tile: st are this lane's eight scores
+// of its row (q . k, -inf where masked); updates the row's reference m_run (log2
+// domain: score * scale) and sum and returns the probabilities, relative to
+// 2^m_run, as the B operand of the second product.  The reference moves, and
+// the accumulators are rescaled (a uniform branch), only when the row's max
+// rises more than kMaxRise above it: until then the probabilities stay below
+// 2^kMaxRise, with the same relative rounding, and the fp32 sums have room.
+constexpr float kMaxRise = 8.f;
+__device__ __forceinline__ bf16x8 softmax_step(const float (&st)[8], float scale, float& m_run, float& l_run, f32x4 (&o)[8]) {
+  float bm = fmaxf(fmaxf(fmaxf(st[0], st[1]), fmaxf(st[2], st[3])), fmaxf(fmaxf(st[4], st[5]), fmaxf(st[6], st[7])));
+  bm = row_max(bm) * scale;
+  const bool rises = bm > m_run + kMaxRise;  // the first valid score does: m_run starts at -inf
+  if (__builtin_amdgcn_ballot_w64(rises)) {
+    const float mn = rises ? bm : m_run;
+    const float alpha = rises ? __builtin_amdgcn_exp2f(m_run - mn) : 1.f;
+    l_run *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
+    m_run = mn;
+  }
+  // the hardware exp2 (v_exp_f32) gives exp2(-inf) = 0 for masked tokens; a
+  // row with nothing valid yet (m_run = -inf) keeps p = 0
+  const float ms = m_run == -INFINITY ? 0.f : m_run;
+  float p[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(st[e], scale, -ms));
+  l_run += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+  u32x4 pp;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) pp[e] = pack_bf16x2(p[2 * e], p[2 * e + 1]);
+  return __builtin_bit_cast(bf16x8, pp);
+}
+
+typedef const __attribute__((address_space(1))) char* gptr;
+__device__ __forceinline__ bf16x8 gld8(gptr p) {
+  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(p));
+}
+
+// Up to 32 query rows (RT = 1 or 2 row tiles).  Each wave takes its own pairs
+// of blocks (pair w, w + 4, ... of the split's; split 0 adds the window block
+// as a last pair of one) for all the rows, straight from memory into MFMA
+// fragments: with one or two row tiles nothing is gained by sharing a block
+// through LDS, and without it the loop has no barriers and no LDS reads.  The
+// loads in flight set the rate (16 to 32 KB per wave, two waves per SIMD); at
+// few blocks per split the chain of dependent accesses (item, page ids,
+// blocks, merge) does.  Against the LDS kernel of four-block chunks with
+// masks and exec changes in its inner loop: 8 sequences of 1024 tokens at 24
+// rows 17.5 -> 13.8 us and at 2 rows (16 heads) 15.7 -> 13.3 us, 64 sequences of
+// ~870 tokens at 20 rows 54.7 -> 50.5 us; 256 sequences of 2400 tokens at 7 rows
+// 214 us, 5.9 TB/s.
+//
+// A pair is 32 tokens: MFMA h of the score product takes, as row r of its A
+// operand, token 8 ((r >> 2) & 1) + 4 h + (r & 3) of block r >> 3, so the lane
+// group g = lane / 16 ends up with the scores of tokens 8 (g & 1) .. + 7 of
+// block g >> 1 (four from each h): its eight probabilities are the B operand
+// of a 16x16x32 MFMA whose A operand is eight consecutive tokens of one dim of
+// a V block, one 16-byte load.
+constexpr int kRegRow = kD + 4;  // LDS row stride of the wave merge, in floats
+template <int RT>
+__global__ __launch_bounds__(256, 2) void attn_reg_kernel(AttnK a) {
+  static_assert(RT == 1 || RT == 2, "one or two row tiles");
+  constexpr int NP = 4;  // waves
+  __shared__ __attribute__((aligned(16))) float s_o[NP][RT * 16 * kRegRow];
+  __shared__ float s_m[NP][RT * 16], s_l[NP][RT * 16];
   const AttnWork item = a.work[blockIdx.x];
   if (item.nsplit == 0) return;  // the list is shorter than the grid
   const int b = item.b, kvh = item.kvh, split = item.split, nsplit = item.nsplit;
-  const int pair = b * a.Hkv + kvh, slot0 = item.slot0;
-  const int G = a.H / a.Hkv, R = a.T * G, RT = (R + 15) / 16;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int G = a.H / a.Hkv, R = a.T * G;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, g = lane >> 4;
-  const int rt = wave % RTW, tp = wave / RTW;
-
   const int ctx = item.ctx >= 0 ? item.ctx : ~item.ctx;
   if (item.ctx < 0 && threadIdx.x == 0 && split == 0) flag_error(a.err, kErrContext);
-  // this split's share of the cached blocks (shares differ by at most one
-  // block); split 0 also takes the window block, as its first chunk: it is in
-  // L2 (just written), so its compute overlaps the first cached chunk's loads
   const int c0 = item.c0, c1 = item.c1;
-  const int ncc = (c1 - c0 + kCB - 1) / kCB;  // cached chunks
-  const int wch = split == 0 ? 1 : 0;         // window chunks
-  const int nchunks = ncc + wch;
+  const int np = (c1 - c0 + 1) / 2;             // pairs of cached blocks
+  const int npw = np + (split == 0 ? 1 : 0);    // and the window
+  const int n = npw > wave ? (npw - wave + NP - 1) / NP : 0;  // this wave's
 
+  // Page ids of 32 of the wave's pairs: lane l holds block l & 1 of pair
+  // idbase + l / 2.  kNoBlock: no such block (or a bad id: any table entry
+  // outside [0, num_blocks) of a block inside the context, -1 included): the
+  // window block's memory is read in its place, and masked out.
+  constexpr int kNoBlock = INT_MIN;
+  int idv = kNoBlock, idbase = 0;
+  bool bad = false;
+  auto read_ids = [&](int j0) {
+    idbase = j0;
+    const int p = wave + NP * (j0 + (lane >> 1)), blk = c0 + 2 * p + (lane & 1);
+    int id = p < np && blk < c1 ? a.table[(size_t)b * a.max_blocks + blk] : kNoBlock;
+    if (id != kNoBlock && (id < 0 || id >= a.num_blocks)) {
+      bad = true;
+      id = kNoBlock;
+    }
+    idv = id;
+  };
+  read_ids(0);
+
+  bf16x8 qf[RT][4];
+  int qpos[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int qc = min(t * 16 + r16, R - 1);  // padding rows repeat the last real row
+    const int i = qc / G, hh = qc % G;
+    const bf16_t* src = a.q + ((size_t)(b * a.T + i) * a.H + kvh * G + hh) * kD + 8 * g;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) qf[t][s] = ld8(src + 32 * s);
+    qpos[t] = i;
+  }
+  const gptr win_k = (gptr)(a.wk + ((size_t)b * a.Hkv + kvh) * (kBlock * kD));
+  const gptr win_v = (gptr)(a.wv + ((size_t)b * a.Hkv + kvh) * (kBlock * kD));
+  const uint32_t kofs = (uint32_t)((8 * ((r16 >> 2) & 1) + (r16 & 3)) * kD + 8 * g) * 2u;
+  const uint32_t vofs = (uint32_t)(r16 * kBlock + 8 * (g & 1)) * 2u;
+
+  // Fragments of two pairs with one row tile, of one pair with two (their
+  // accumulators leave no room for more): the next pair's K then loads under
+  // this one's softmax and second product, its V from there on.
+  constexpr int NS = RT == 1 ? 2 : 1;
+  bf16x8 kf[NS][8], vf[NS][8];
+  // this lane's block of pair j in the pages (kp or vp), the window block if it has none
+  auto page = [&](const bf16_t* pages, gptr win, int j, bool second) {
+    const int ia = __builtin_amdgcn_readlane(idv, 2 * (j - idbase)), ib = __builtin_amdgcn_readlane(idv, 2 * (j - idbase) + 1);
+    const gptr pa = ia >= 0 ? (gptr)pages + ((size_t)ia * a.Hkv + kvh) * (kBlock * kD * 2) : win;
+    const gptr pb = ib >= 0 ? (gptr)pages + ((size_t)ib * a.Hkv + kvh) * (kBlock * kD * 2) : win;
+    return second ? pb : pa;
+  };
+  auto load_k = [&](auto setc, int j) {
+    const gptr kl = page(a.kp, win_k, j, (r16 & 8) != 0) + kofs;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) kf[decltype(setc)::value % NS][h * 4 + s] = gld8(kl + h * (4 * kD * 2) + s * 64);
+  };
+  auto load_v = [&](auto setc, int j) {
+    const gptr vl = page(a.vp, win_v, j, (g & 2) != 0) + vofs;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) vf[decltype(setc)::value % NS][dt] = gld8(vl + dt * (16 * kBlock * 2));
+  };
+
+  float m_run[RT], l_run[RT];
+  f32x4 o[RT][8];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    m_run[t] = -INFINITY;
+    l_run[t] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  // Pair j, its fragments in set j % NS.  The loads of the pair that takes over
+  // the set go out as soon as it is free (the order is
+  // pinned: hoisted loads would need registers of their own), past the wave's
+  // last pair too (they read the window block): loads that may or may not
+  // have been issued would make the compiler wait for every load in flight.
+  auto step = [&](auto setc, int j) {
+    constexpr int set = decltype(setc)::value % NS;
+    const bool last = j == n - 1;  // this pair may hold fewer than 32 tokens, or be the window's
+    int lim[RT];
+    if (last) {
+      // nv valid tokens among this lane's eight; the window is causal besides.
+      // V past the valid tokens may hold anything: zero it.
+      const int p = wave + NP * j, blk = c0 + 2 * p + (g >> 1);
+      const bool win = p >= np;
+      const int v = win ? (g < 2 ? a.T : 0) : (blk < c1 ? min(kBlock, ctx - blk * kBlock) : 0);
+      const int nv = v - 8 * (g & 1);
+#pragma unroll
+      for (int t = 0; t < RT; ++t) lim[t] = win ? min(nv, qpos[t] + 1 - 8 * (g & 1)) : nv;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t keep = nv >= 2 * e + 2 ? 0xffffffffu : nv == 2 * e + 1 ? 0xffffu : 0u;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) {
+          u32x4 w = __builtin_bit_cast(u32x4, vf[set][dt]);
+          w[e] &= keep;
+          vf[set][dt] = __builtin_bit_cast(bf16x8, w);
+        }
+      }
+    }
+    f32x4 st[RT][2];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) st[t][0] = st[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          st[t][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[set][h * 4 + s], qf[t][s], st[t][h], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (j + NS - idbase >= 32) read_ids(j + NS);
+    load_k(setc, j + NS);
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 pf[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      float sc[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sc[e] = st[t][e / 4][e % 4];
+      if (last) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sc[e] = e < lim[t] ? sc[e] : -INFINITY;
+      }
+      pf[t] = softmax_step(sc, a.scale_log2, m_run[t], l_run[t], o[t]);
+    }
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+        o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[set][dt], pf[t], o[t][dt], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_v(setc, j + NS);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  constexpr std::integral_constant<int, 0> s0{};
+  constexpr std::integral_constant<int, 1> s1{};
+  load_k(s0, 0);
+  load_v(s0, 0);
+  if constexpr (NS == 2) {
+    load_k(s1, 1);
+    load_v(s1, 1);
+  }
+  for (int j = 0; j < n; ++j) {
+    step(s0, j);
+    if constexpr (NS == 2) {
+      if (++j >= n) break;
+      step(s1, j);
+    }
+  }
+  if (__builtin_amdgcn_ballot_w64(bad) && lane == 0) flag_error(a.err, kErrBlock);
+
+  // merge the waves, then store the rows or this split's partial
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    float ls = l_run[t];
+    ls += __shfl_xor(ls, 16);
+    ls += __shfl_xor(ls, 32);
+    if (g == 0) {
+      s_m[wave][t * 16 + r16] = m_run[t];
+      s_l[wave][t * 16 + r16] = ls;
+    }
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f32x4*>(&s_o[wave][(t * 16 + r16) * kRegRow + 16 * dt + 4 * g]) = o[t][dt];
+  }
+  __syncthreads();
+  const int slot0 = item.slot0;
   const __amdgpu_buffer_rsrc_t ors = coherent_rsrc(a.part_o, a.part_o_bytes);
   const __amdgpu_buffer_rsrc_t mrs = coherent_rsrc(a.part_ml, a.part_ml_bytes);
-  if (nchunks == 0) {  // no blocks of this sequence for this split: mark its rows empty for the merge
-    for (int qr = threadIdx.x; qr < R; qr += 256)
-      coherent_store_f32(mrs, (uint32_t)(((((size_t)slot0 + split) * (RT * 16) + qr) * 2) * 4), -INFINITY);
-    split_arrive(a, pair, nsplit, slot0, R, RT, G, b, kvh, ors, mrs, reinterpret_cast<float*>(smem),
-                 (int)(sizeof(smem) / sizeof(float)));
-    return;
+  for (int u = threadIdx.x; u < R * (kD / 4); u += 256) {
+    const int qr = u / (kD / 4), d = (u % (kD / 4)) * 4;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NP; ++w) mx = fmaxf(mx, s_m[w][qr]);
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    float wsum = 0.f;
+#pragma unroll
+    for (int w = 0; w < NP; ++w)
+      if (s_m[w][qr] != -INFINITY) {  // a wave without pairs holds zeros anyway
+        const float f = exp2f(s_m[w][qr] - mx);
+        wsum += f * s_l[w][qr];
+        acc += f * *reinterpret_cast<const f32x4*>(&s_o[w][qr * kRegRow + d]);
+      }
+    if (nsplit == 1) {
+      const int i = qr / G, hh = qr % G;
+      const float inv = 1.0f / wsum;
+      u32x2 ov;
+      ov[0] = pack_bf16x2(acc[0] * inv, acc[1] * inv);
+      ov[1] = pack_bf16x2(acc[2] * inv, acc[3] * inv);
+      *out_at(a, b * a.T + i, (kvh * G + hh) * kD + d) = ov;
+    } else {
+      const size_t row = ((size_t)slot0 + split) * (RT * 16) + qr;
+      coherent_store(ors, (uint32_t)((row * kD + d) * 4), acc);
+      if (d == 0) {
+        coherent_store_f32(mrs, (uint32_t)(row * 8), mx);
+        coherent_store_f32(mrs, (uint32_t)(row * 8 + 4), wsum);
+      }
+    }
   }
+  if (nsplit > 1) split_arrive(a, b * a.Hkv + kvh, nsplit, slot0, R, RT, G, b, kvh, ors, mrs);
+}
+
+// 33 to 64 query rows (three or four row tiles, one per wave).  The four waves
+// share every block, so the pairs are streamed through LDS (kPairBuf buffers of
+// one pair, 16 KB; kPairBuf - 1 pairs in flight, no registers held by them) and
+// each wave multiplies every pair by its own row tile, with the token order of
+// attn_reg_kernel.  Loads go from memory straight into LDS
+// (global_load_lds_dwordx4: lane i's 16 bytes land at byte 16 i of the
+// instruction's KB, so each lane fetches the global piece that the swizzled
+// layout keeps there); each wave loads one of a pair's four 4 KB pieces (K and
+// V of two blocks).  96 KB per CU in flight and ~1000 clocks of work per wave
+// and pair: 256 sequences of 2400 tokens at 56 rows 272 -> 241 us (5.2 TB/s)
+// against four-block chunks with two chunk buffers and 16x16x16 MFMAs.  One
+// wave per SIMD with all four row tiles in registers was slower (392 us: the
+// fragments pass through accumulation registers), as was reading the blocks
+// from memory once per two row tiles (280 us).
+//
+// Swizzle, in 16-byte units, so that the 16 lanes of a fragment read's phase
+// (one g, all r16) hit 16 different positions of the 256 bytes of LDS banks:
+// K row `tok` of block `blk` keeps unit u at u ^ tok ^ 4 blk (the 16 rows of
+// one MFMA are 8 tokens of each block, and their tok ^ 4 blk are all
+// different); V dim d keeps its two halves swapped when bit 3 of d is set.
+constexpr int kPairBuf = 4;
+constexpr int kPairBytes = 4 * kBlock * kD * 2;  // K of both blocks, then V of both
+__global__ __launch_bounds__(256, 2) void attn_lds_kernel(AttnK a) {
+  __shared__ __attribute__((aligned(16))) char smem[kPairBuf * kPairBytes];
+  const AttnWork item = a.work[blockIdx.x];
+  if (item.nsplit == 0) return;  // the list is shorter than the grid
+  const int b = item.b, kvh = item.kvh, split = item.split, nsplit = item.nsplit;
+  const int G = a.H / a.Hkv, R = a.T * G, RT = (R + 15) / 16;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r16 = lane & 15, g = lane >> 4;
+  const int ctx = item.ctx >= 0 ? item.ctx : ~item.ctx;
+  if (item.ctx < 0 && threadIdx.x == 0 && split == 0) flag_error(a.err, kErrContext);
+  const int c0 = item.c0, c1 = item.c1;
+  const int np = (c1 - c0 + 1) / 2;           // pairs of cached blocks
+  const int n = np + (split == 0 ? 1 : 0);    // and the window
+
+  // This wave's piece of a pair: block second of it, K (waves 0, 1) or V (2, 3)
+  const int second = wave & 1;
+  const bool is_v = wave >= 2;
+  // Page ids of its block of 64 pairs, pair idbase + lane; kNoBlock (no such
+  // block, or a bad id: any table entry outside [0, num_blocks) of a block
+  // inside the context, -1 included): the window block's memory is read
+  // instead, and masked out.
+  constexpr int kNoBlock = INT_MIN;
+  int idv = kNoBlock, idbase = 0;
+  bool bad = false;
+  auto read_ids = [&](int p0) {
+    idbase = p0;
+    const int blk = c0 + 2 * (p0 + lane) + second;
+    int id = p0 + lane < np && blk < c1 ? a.table[(size_t)b * a.max_blocks + blk] : kNoBlock;
+    if (id != kNoBlock && (id < 0 || id >= a.num_blocks)) {
+      bad = true;
+      id = kNoBlock;
+    }
+    idv = id;
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): no load of the compiler's is left for the loop to wait for
+  };
+  uint32_t lofs[4];  // byte offsets in the 4 KB block that this lane's pieces come from
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int tok = 4 * i + (lane >> 4), dim = 32 * i + (lane >> 1);
+    lofs[i] = is_v ? (uint32_t)(dim * 32 + ((lane & 1) ^ ((dim >> 3) & 1)) * 16)
+                   : (uint32_t)(tok * 256 + (((lane & 15) ^ tok ^ (4 * second)) & 15) * 16);
+  }
+  const bf16_t* win = (is_v ? a.wv : a.wk) + ((size_t)b * a.Hkv + kvh) * (kBlock * kD);
+  const bf16_t* pages = is_v ? a.vp : a.kp;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+  auto issue = [&](int p) {  // pair p (past the last one: the window block again) into buffer p % kPairBuf
+    if (p - idbase >= 64) read_ids(p);
+    const int id = __builtin_amdgcn_readlane(idv, p - idbase);
+    const bf16_t* src = id >= 0 ? pages + ((size_t)id * a.Hkv + kvh) * (kBlock * kD) : win;
+    const uint32_t dst = lds0 + (uint32_t)((p % kPairBuf) * kPairBytes + wave * (kBlock * kD * 2));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lofs[i]), "s"(src), "s"(dst + i * 1024)
+                   : "memory", "m0");
+  };
+
   bf16x8 qf[4];
   int qpos;
+  {
+    const int qc = min(wave * 16 + r16, R - 1);  // padding rows repeat the last real row
+    const int i = qc / G, hh = qc % G;
+    const bf16_t* src = a.q + ((size_t)(b * a.T + i) * a.H + kvh * G + hh) * kD + 8 * g;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) qf[s] = ld8(src + 32 * s);
+    qpos = i;
+  }
+  read_ids(0);  // (waits for the queries too)
+#pragma unroll
+  for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(qf[s]));
+  for (int p = 0; p < kPairBuf - 1; ++p) issue(p);
+
+  // fragment read offsets in a buffer
+  uint32_t kofs[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int blk = r16 >> 3, tok = 8 * ((r16 >> 2) & 1) + 4 * h + (r16 & 3);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      kofs[h][s] = (uint32_t)(blk * (kBlock * kD * 2) + tok * 256 + (((4 * s + g) ^ tok ^ (4 * blk)) & 15) * 16);
+  }
+  const uint32_t vofs = (uint32_t)((2 + (g >> 1)) * (kBlock * kD * 2) + r16 * 32 + (((g & 1) ^ (r16 >> 3)) & 1) * 16);
+
   float m_run = -INFINITY, l_run = 0.f;
   f32x4 o[8];
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // chunk ch: blocks [j0, j0 + nblk) of the cached range, or the window block
-  auto chunk_blocks = [&](int ch, int& j0, int& nblk) {
-    if (ch >= wch) {
-      j0 = c0 + (ch - wch) * kCB;
-      nblk = min(kCB, c1 - j0);
-    } else {
-      j0 = -1;
-      nblk = 1;
-    }
-  };
-  // Chunk loads go from memory straight into LDS (global_load_lds_dwordx4):
-  // a block is 4 K and 4 V instructions of 1 KB, loaded by one wave (chunks
-  // of 4 blocks) or by two (K and V; chunks of 2), and
-  // lane i's 16 bytes land at byte 16 i of the instruction's KB -- so each lane
-  // fetches the global piece that the swizzled layout keeps there.  NBUF
-  // buffers, NBUF-1 chunks in flight.  A block's page id is read with a scalar
-  // load one chunk before its pages; blocks past the chunk, or with a bad id,
-  // load the window block (valid memory, never read as cache).  Every chunk
-  // issues the same UPW loads per wave, so the wait counts below are exact.
-  const int wv = __builtin_amdgcn_readfirstlane(wave);
-  uint32_t kofs[4], vofs[4];
+  for (int p = 0; p < n; ++p) {
+    // this wave's piece of pair p has landed once at most the later
+    // kPairBuf - 2 pairs' loads are outstanding; after the barrier every
+    // wave's has, and every wave is done with pair p - 1, whose buffer takes
+    // pair p + kPairBuf - 1
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kPairBuf - 2) * 4) : "memory");
+    issue(p + kPairBuf - 1);
+    if (wave >= RT) continue;  // uniform
+    const char* buf = smem + (p % kPairBuf) * kPairBytes;
+    bf16x8 kf[2][4], vf[8];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int tok = 4 * j + (lane >> 4), slot = lane & 15;
-    kofs[j] = (uint32_t)(tok * kD + ((slot ^ tok) & 15) * 8) * 2u;
-    const int dim = 32 * j + (lane >> 1), hv = (lane & 1) ^ ((dim >> 3) & 1);
-    vofs[j] = (uint32_t)(dim * kBlock + hv * 8) * 2u;
-  }
-  const bf16_t* win_k = a.wk + ((size_t)b * a.Hkv + kvh) * (kBlock * kD);
-  const bf16_t* win_v = a.wv + ((size_t)b * a.Hkv + kvh) * (kBlock * kD);
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
-  bool bad = false;
-  // Page ids: lane l of wave w holds the id of block w of cached chunk
-  // idbase + l, read 64 chunks at a time (a split longer than 64 chunks
-  // reloads, waiting for its loads in flight); a chunk's id is then a lane
-  // read, with no memory access in the loop.  kNoBlock (not a table value):
-  // load the window block.  Any table entry outside [0, num_blocks) of a block
-  // inside the context, -1 included, is a bad block.
-  constexpr int kNoBlock = INT_MIN;
-  int idv = kNoBlock, idbase = -64;
-  auto block_id = [&](int ch) {
-    if (ch < wch || ch >= nchunks) return kNoBlock;
-    const int cc = ch - wch;
-    if (cc - idbase >= 64) {
-      idbase = cc;
-      const int blk = c0 + (cc + lane) * kCB + wv / WPB;
-      idv = (cc + lane < ncc && blk < c1) ? a.table[(size_t)b * a.max_blocks + blk] : kNoBlock;
-      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-    }
-    return __builtin_amdgcn_readlane(idv, cc - idbase);
-  };
-  auto issue = [&](int ch, int id) {
-    const int buf = ch % NBUF;
-    int ph = __builtin_amdgcn_readfirstlane(id);
-    if (ph != kNoBlock && (ph < 0 || ph >= a.num_blocks)) {
-      bad = true;
-      ph = kNoBlock;
-    }
-    const size_t off = ((size_t)max(ph, 0) * a.Hkv + kvh) * (kBlock * kD);
-    const bf16_t* kb = ph >= 0 ? a.kp + off : win_k;
-    const bf16_t* vb = ph >= 0 ? a.vp + off : win_v;
-    const uint32_t kd = lds0 + (uint32_t)(buf * 2 * KV_ELEMS + (wv / WPB) * kBlock * kD) * 2u;
-    const uint32_t vd = kd + (uint32_t)KV_ELEMS * 2u;
-    if (WPB == 1 || wv % 2 == 0) {
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(kofs[j]), "s"(kb), "s"(kd + j * 1024)
-                     : "memory", "m0");
-    }
-    if (WPB == 1 || wv % 2 == 1) {
+      for (int h = 0; h < 2; ++h) kf[h][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(buf + kofs[h][s]));
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(vofs[j]), "s"(vb), "s"(vd + j * 1024)
-                     : "memory", "m0");
-    }
-  };
-  for (int d = 0; d < NBUF - 1; ++d) issue(d, block_id(d));
-  int ph_pre = block_id(NBUF - 1);
-  // q after the prologue's chunks, and a wait the compiler sees: from here on
-  // no load of its own is outstanding, so it adds no load waits in the loop
-  // (which would also wait for the chunks in flight)
-  {
-    const int qc = min(rt * 16 + r16, R - 1);  // padding rows repeat the last real row
-    const int i = qc / G, hh = qc % G;
-    const bf16_t* src = a.q + ((size_t)(b * a.T + i) * a.H + kvh * G + hh) * kD + 32 * g;
+    for (int dt = 0; dt < 8; ++dt) vf[dt] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(buf + vofs + dt * 512));
+    f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int s = 0; s < 4; ++s) qf[s] = ld8(src + 8 * s);
-    qpos = i;
-  }
-  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-  for (int ch = 0; ch < nchunks; ++ch) {
-    // this wave's loads of chunk ch have landed once at most the later
-    // NBUF-2 chunks' are outstanding; after the barrier every wave's have, and
-    // every wave is done with chunk ch-1, whose buffer takes chunk ch+NBUF-1
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NBUF - 2) * UPW) : "memory");
-    issue(ch + NBUF - 1, ph_pre);
-    ph_pre = block_id(ch + NBUF);
-    int j0, nblk;
-    chunk_blocks(ch, j0, nblk);
-    const bool win = j0 < 0;
-    const bf16_t* ks = smem + (ch % NBUF) * 2 * KV_ELEMS;
-    const bf16_t* vs = ks + KV_ELEMS;
-    if (rt < RT) {
-      // Blocks bi and bi + NTP together: their score products are two
-      // independent chains, and one cross-lane max, one exp2 of the running
-      // max and one rescale of the accumulators serve both.
-      for (int bi = tp; bi < nblk; bi += 2 * NTP) {
-        const bool two = bi + NTP < nblk;  // uniform
-        bf16x8 kf[2][4];
-        u32x2 vf[2][8];
-        int nvalid[2];
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          if (h == 1 && !two) break;
-          const int blk = bi + h * NTP;
-          nvalid[h] = win ? a.T : min(kBlock, ctx - (j0 + blk) * kBlock);
-          const bf16_t* kb = ks + blk * kBlock * kD;
-          const bf16_t* vb = vs + blk * kBlock * kD;
+      for (int h = 0; h < 2; ++h) st[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[h][s], qf[s], st[h], 0, 0, 0);
+    float sc[8];
 #pragma unroll
-          for (int s = 0; s < 4; ++s) kf[h][s] = ld8(kb + k_lds(r16, 4 * g + s));
+    for (int e = 0; e < 8; ++e) sc[e] = st[e / 4][e % 4];
+    if (p >= np - 1) {
+      // the last cached pair may hold fewer than 32 tokens; the window is
+      // causal.  V past the valid tokens may hold anything: zero it.
+      const int blk = c0 + 2 * p + (g >> 1);
+      const bool w = p >= np;
+      const int v = w ? (g < 2 ? a.T : 0) : (blk < c1 ? min(kBlock, ctx - blk * kBlock) : 0);
+      const int nv = v - 8 * (g & 1), lim = w ? min(nv, qpos + 1 - 8 * (g & 1)) : nv;
 #pragma unroll
-          for (int dt = 0; dt < 8; ++dt) vf[h][dt] = *reinterpret_cast<const u32x2*>(vb + v_lds(16 * dt + r16, g));
-          if (4 * g + 3 >= nvalid[h]) {  // tokens past the valid ones may hold anything: zero them
-            const int keep = nvalid[h] - 4 * g;
+      for (int e = 0; e < 8; ++e) sc[e] = e < lim ? sc[e] : -INFINITY;
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
-              uint32_t lo = vf[h][dt][0], hi = vf[h][dt][1];
-              if (keep <= 0) lo = 0u;
-              else if (keep == 1) lo &= 0xffffu;
-              if (keep <= 2) hi = 0u;
-              else if (keep == 3) hi &= 0xffffu;
-              vf[h][dt][0] = lo;
-              vf[h][dt][1] = hi;
-            }
-          }
-        }
-        f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          st[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0][s], qf[s], st[0], 0, 0, 0);
-          if (two) st[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[1][s], qf[s], st[1], 0, 0, 0);
-        }
-        float sc[2][4];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) sc[h][i] = st[h][i] * a.scale_log2;
-          if (h == 1 && !two) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) sc[h][i] = -INFINITY;
-          } else if (win || nvalid[h] < kBlock) {  // uniform: only a partial or the window block masks tokens
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int tok = 4 * g + i;
-              if (!(tok < nvalid[h] && (!win || tok <= qpos))) sc[h][i] = -INFINITY;
-            }
-          }
-        }
-        float bm = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
-                         fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
-        bm = fmaxf(bm, __shfl_xor(bm, 16));
-        bm = fmaxf(bm, __shfl_xor(bm, 32));
-        const float mn = fmaxf(m_run, bm);
-        // exponents are <= 0 here: the hardware exp2 (v_exp_f32) gives
-        // exp2(-inf) = 0 for masked tokens; a row with nothing valid yet
-        // (mn = -inf) keeps p = 0
-        const float ms = mn == -INFINITY ? 0.f : mn;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - ms);
-        float p[2][4];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) p[h][i] = __builtin_amdgcn_exp2f(sc[h][i] - ms);
-        l_run = l_run * alpha + (((p[0][0] + p[0][1]) + (p[0][2] + p[0][3])) + ((p[1][0] + p[1][1]) + (p[1][2] + p[1][3])));
-        m_run = mn;
-        bf16x4 pf[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          u32x2 pp;
-          pp[0] = pack_bf16x2(p[h][0], p[h][1]);
-          pp[1] = pack_bf16x2(p[h][2], p[h][3]);
-          pf[h] = __builtin_bit_cast(bf16x4, pp);
-        }
-        // the accumulators move only when some row's running max rose (uniform branch)
-        if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {
-#pragma unroll
-          for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
-        }
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t keep = nv >= 2 * e + 2 ? 0xffffffffu : nv == 2 * e + 1 ? 0xffffu : 0u;
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) {
-          o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, vf[0][dt]), pf[0], o[dt], 0, 0, 0);
-          if (two)
-            o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, vf[1][dt]), pf[1], o[dt], 0, 0, 0);
+          u32x4 x = __builtin_bit_cast(u32x4, vf[dt]);
+          x[e] &= keep;
+          vf[dt] = __builtin_bit_cast(bf16x8, x);
         }
       }
     }
+    const bf16x8 pf = softmax_step(sc, a.scale_log2, m_run, l_run, o);
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[dt], pf, o[dt], 0, 0, 0);
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the surplus loads, before LDS is reused
-  __syncthreads();
-  if (bad && lane == 0) flag_error(a.err, kErrBlock);  // bad is per wave
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the surplus loads, before the workgroup ends
+  if (__builtin_amdgcn_ballot_w64(bad) && lane == 0) flag_error(a.err, kErrBlock);
 
-  // merge the token phases of each row tile (LDS reused), then store or write partials
-  float* s_o = reinterpret_cast<float*>(smem);  // [NTP][kD][17]
-  float* s_m = s_o + NTP * kD * 17;             // [NTP][16]
-  float* s_l = s_m + NTP * 16;
-  for (int t = 0; t < RT; ++t) {
-    if (rt == t) {
-      float lsum = l_run;
-      lsum += __shfl_xor(lsum, 16);
-      lsum += __shfl_xor(lsum, 32);
+  // every wave holds its rows whole: lane (r16, g) has dims 16 dt + 4 g .. + 3 of row r16
+  const int slot0 = item.slot0;
+  const __amdgpu_buffer_rsrc_t ors = coherent_rsrc(a.part_o, a.part_o_bytes);
+  const __amdgpu_buffer_rsrc_t mrs = coherent_rsrc(a.part_ml, a.part_ml_bytes);
+  float lsum = l_run;
+  lsum += __shfl_xor(lsum, 16);
+  lsum += __shfl_xor(lsum, 32);
+  const int qr = wave * 16 + r16;
+  if (qr < R) {
+    if (nsplit == 1) {
+      const int i = qr / G, hh = qr % G;
+      const float inv = 1.0f / lsum;
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt)
+      for (int dt = 0; dt < 8; ++dt) {
+        u32x2 ov;
+        ov[0] = pack_bf16x2(o[dt][0] * inv, o[dt][1] * inv);
+        ov[1] = pack_bf16x2(o[dt][2] * inv, o[dt][3] * inv);
+        *out_at(a, b * a.T + i, (kvh * G + hh) * kD + 16 * dt + 4 * g) = ov;
+      }
+    } else {
+      const size_t row = ((size_t)slot0 + split) * (RT * 16) + qr;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s_o[(tp * kD + 16 * dt + 4 * g + i) * 17 + r16] = o[dt][i];
+      for (int dt = 0; dt < 8; ++dt) coherent_store(ors, (uint32_t)((row * kD + 16 * dt + 4 * g) * 4), o[dt]);
       if (g == 0) {
-        s_m[tp * 16 + r16] = m_run;
-        s_l[tp * 16 + r16] = lsum;
+        coherent_store_f32(mrs, (uint32_t)(row * 8), m_run);
+        coherent_store_f32(mrs, (uint32_t)(row * 8 + 4), lsum);
       }
     }
-    __syncthreads();
-    // thread: 4 consecutive head dims of one query row per unit (2 units)
-    for (int u = threadIdx.x; u < 16 * (kD / 4); u += 256) {
-      const int qr16 = u / (kD / 4), d = (u % (kD / 4)) * 4;
-      const int qr = t * 16 + qr16;
-      float mx = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < NTP; ++w) mx = fmaxf(mx, s_m[w * 16 + qr16]);
-      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-      float wsum = 0.f;
-      if (mx != -INFINITY) {
-#pragma unroll
-        for (int w = 0; w < NTP; ++w) {
-          const float f = (s_m[w * 16 + qr16] == -INFINITY) ? 0.f : exp2f(s_m[w * 16 + qr16] - mx);
-          wsum += f * s_l[w * 16 + qr16];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] += f * s_o[(w * kD + d + e) * 17 + qr16];
-        }
-      }
-      if (qr < R) {
-        if (nsplit == 1) {
-          const int i = qr / G, hh = qr % G;
-          u32x2 ov;
-          ov[0] = pack_bf16x2(acc[0] / wsum, acc[1] / wsum);
-          ov[1] = pack_bf16x2(acc[2] / wsum, acc[3] / wsum);
-          *out_at(a, b * a.T + i, (kvh * G + hh) * kD + d) = ov;
-        } else {
-          const size_t base = ((size_t)slot0 + split) * (RT * 16) + qr;
-          coherent_store(ors, (uint32_t)((base * kD + d) * 4), acc);
-          if (d == 0) {
-            coherent_store_f32(mrs, (uint32_t)(base * 2 * 4), mx);
-            coherent_store_f32(mrs, (uint32_t)((base * 2 + 1) * 4), wsum);
-          }
-        }
-      }
-    }
-    __syncthreads();
   }
-  if (nsplit > 1)
-    split_arrive(a, pair, nsplit, slot0, R, RT, G, b, kvh, ors, mrs, reinterpret_cast<float*>(smem),
-                 (int)(sizeof(smem) / sizeof(float)));
+  if (nsplit > 1) split_arrive(a, b * a.Hkv + kvh, nsplit, slot0, R, RT, G, b, kvh, ors, mrs);
 }
 
 // fp32 path: one workgroup per (sequence, query head, window position); scores
@@ -629,12 +745,12 @@ int attention_plan(int B, int Hkv, int max_blocks) {
   // 7B shape at B=256 k=7 fastest with 128 extra, B=8 with 512).
   const int pairs = B * Hkv;
   const long cap = (long)pairs * std::max(1, (max_blocks + kMinSplitBlocks - 1) / kMinSplitBlocks);
-  const int extra = 2 * pairs <= attn_wgs_per_cu(kAttnBuf, kAttnChunk) * device_cus() ? kExtraWorkgroups
+  const int extra = 2 * pairs <= kAttnWgsPerCu * device_cus() ? kExtraWorkgroups
                                                                                       : std::min(kExtraWorkgroups, kExtraWorkgroupsLarge);
   return (int)std::max<long>(pairs, std::min<long>((long)pairs + extra, cap));
 }
 
-bool attention_orders(int nwg) { return nwg > attn_wgs_per_cu(kAttnBuf, kAttnChunk) * device_cus(); }
+bool attention_orders(int nwg) { return nwg > kAttnWgsPerCu * device_cus(); }
 
 size_t attention_work_bytes(int B, int Hkv) { return (size_t)(B * Hkv + kExtraWorkgroups) * sizeof(AttnWork); }
 
@@ -687,9 +803,9 @@ hipError_t launch_attention(const AttnArgs& x, hipStream_t s) {
   if (!x.work || x.wgs < x.B * x.Hkv || x.wgs > x.B * x.Hkv + kExtraWorkgroups) return hipErrorInvalidValue;
   dim3 grid(x.wgs);
   switch (RT) {
-    case 1: hipLaunchKernelGGL((attn_lds_kernel<1, kAttnBuf, kAttnChunk>), grid, dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL((attn_lds_kernel<2, kAttnBuf, kAttnChunk>), grid, dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((attn_lds_kernel<4, kAttnBuf, kAttnChunk>), grid, dim3(256), 0, s, a); break;
+    case 1: hipLaunchKernelGGL(attn_reg_kernel<1>, grid, dim3(256), 0, s, a); break;
+    case 2: hipLaunchKernelGGL(attn_reg_kernel<2>, grid, dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL(attn_lds_kernel, grid, dim3(256), 0, s, a); break;
   }
   return hipGetLastError();
 }

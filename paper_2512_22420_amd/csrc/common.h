@@ -52,6 +52,9 @@ __device__ __forceinline__ void coherent_store_f32(__amdgpu_buffer_rsrc_t r, uin
 __device__ __forceinline__ float coherent_load_f32(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, byte_off, 0, 16 /* sc1 */));
 }
+__device__ __forceinline__ float2 coherent_load_f32x2(__amdgpu_buffer_rsrc_t r, uint32_t byte_off) {
+  return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, 0, 16 /* sc1 */));
+}
 __device__ __forceinline__ void coherent_store_f64(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, double v) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, byte_off, 0, 16 /* sc1 */);
 }

@@ -105,6 +105,9 @@ def _attn_gpu(shape, c, q, wk, wv, ctx, k, table=None):
     return _host(out, shape.dtype).reshape(B * T, shape.n_heads, shape.head_dim), err
 
 
+EDGES = [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513]
+
+
 def _many(B, seed):
     """B short contexts (0..40 tokens) with every 50th one long (1500..2047): the
     work list gives the long ones several splits and the short ones one."""
@@ -121,13 +124,18 @@ def _many(B, seed):
     (L8, [0], 0),                                 # window only, one row
     (QW, [300, 0, 47, 4000], 8),                  # G = 7: 63 query rows
     (QW, [129, 1], 2),
+    (L8, EDGES, 0),                               # 4 rows; partial, odd and even block counts in every position
+    (L8, EDGES, 7),                               # 32 rows: the most the kernel without LDS takes
+    (L8, EDGES, 8),                               # 36 rows: the fewest of the LDS kernel (three row tiles)
+    (L8, EDGES, 11),                              # 48 rows
     (TF, [32, 48, 0], 3),                         # fp32 path
     (dataclasses.replace(TF, head_dim=136, n_heads=2, n_kv_heads=1), [1, 17, 1100, 16], 2),  # fp32: over 64 blocks, over 128 dims
     (L8, _many(64, 3), 4),                        # work list: the one-wave path at its largest batch
     (L8, _many(65, 4), 2),                        # work list: the block-wide path at its smallest batch
     (L8, _many(600, 1), 3),                       # work list: more sequences than half its threads
     (L8, _many(1100, 2), 1),                      # work list: five sequences per thread (contexts re-read)
-], ids=["8b-ragged", "8b-r64", "8b-headline", "8b-window-only", "g7-r63", "g7-k2", "f32", "f32-long-wide", "8b-b64-work-list",
+], ids=["8b-ragged", "8b-r64", "8b-headline", "8b-window-only", "g7-r63", "g7-k2", "8b-edges-r4", "8b-edges-r32", "8b-edges-r36",
+        "8b-edges-r48", "f32", "f32-long-wide", "8b-b64-work-list",
         "8b-b65-work-list", "8b-b600-work-list", "8b-b1100-work-list"])
 def test_attn_verify_matches_oracle(shape, ctx, k):
     ctx = np.asarray(ctx, np.int32)
@@ -223,3 +231,47 @@ def test_rmsnorm_rope_matches_oracle(shape, ctx, k):
         assert r.max() <= tol, r.max()
     # slots past the window are zero
     assert np.all(gk[:, :, T:, :] == 0) and np.all(gv[:, :, :, T:] == 0)
+
+
+@pytest.mark.parametrize("shape,B,ctx,k", [
+    (L8, 64, 8200, 3),    # splits of over 256 blocks: the kernel without LDS re-reads its page ids
+    (QW, 128, 4300, 7),   # splits of over 128 blocks: the LDS kernel does
+], ids=["8b-b64", "7b-b128"])
+def test_attn_splits_longer_than_the_page_ids_read_at_once(shape, B, ctx, k):
+    """Few workgroups per sequence and long contexts; three sequences are checked
+    against attention in 64 bits on the device."""
+    T, H, Hkv, D = k + 1, shape.n_heads, shape.n_kv_heads, shape.head_dim
+    G = H // Hkv
+    one = dataclasses.replace(shape, n_layers=1)
+    ctxs = np.full(B, ctx, np.int32) - np.arange(B, dtype=np.int32)
+    table, nblk, mb = W.make_block_table(one, ctxs, k, seed=3)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    kp, vp = (x[0] for x in W.device_pages(one, nblk, gen))
+    q = W.device_normal_bf16(gen, (B * T, H, D), 1.0)
+    wk = torch.zeros((B, Hkv, 16, D), dtype=torch.int16, device="cuda")
+    wv = torch.zeros((B, Hkv, D, 16), dtype=torch.int16, device="cuda")
+    wk[:, :, :T] = W.device_normal_bf16(gen, (B, Hkv, T, D), 0.5)
+    wv[..., :T] = W.device_normal_bf16(gen, (B, Hkv, D, T), 0.5)
+    desc = model_desc(shape)
+    n = nb.attn_workspace_bytes(desc, B, k)
+    ws = _ws(n)
+    bt, cl = torch.from_numpy(table).cuda(), torch.from_numpy(ctxs).cuda()
+    out = torch.empty((B * T, H * D), dtype=torch.int16, device="cuda")
+    nb.attn_verify(desc, q.data_ptr(), kp.data_ptr(), vp.data_ptr(), nblk, wk.data_ptr(), wv.data_ptr(), bt.data_ptr(), mb,
+                   cl.data_ptr(), B, k, out.data_ptr(), ws.data_ptr(), n, _s())
+    assert nb.device_error(ws.data_ptr(), n, _s()) == 0
+    wide = lambda t: t.view(torch.bfloat16).double()
+    for b in (0, B // 2, B - 1):
+        c = int(ctxs[b])
+        blocks = bt[b, : (c + 15) // 16].long()
+        kk = torch.cat([wide(kp[blocks]).permute(1, 0, 2, 3).reshape(Hkv, -1, D)[:, :c], wide(wk[b])[:, :T]], 1)
+        vv = torch.cat([wide(vp[blocks]).permute(1, 0, 3, 2).reshape(Hkv, -1, D)[:, :c],
+                        wide(wv[b])[..., :T].transpose(1, 2)], 1)
+        qb = wide(q[b * T: (b + 1) * T]).view(T, Hkv, G, D).permute(1, 2, 0, 3)
+        s = torch.matmul(qb.reshape(Hkv, G * T, D), kk.transpose(1, 2).contiguous()).view(Hkv, G, T, c + T) / D ** 0.5
+        s = s.masked_fill(torch.arange(c + T, device="cuda")[None] > c + torch.arange(T, device="cuda")[:, None], -torch.inf)
+        ref = torch.matmul(torch.softmax(s, -1).view(Hkv, G * T, c + T), vv).view(Hkv, G, T, D).permute(2, 0, 1, 3)
+        got = wide(out[b * T: (b + 1) * T]).view(T, Hkv, G, D)
+        # bf16 probabilities and output: 2^-9 relative roundings
+        assert float((got - ref).norm() / ref.norm()) < 5e-3
