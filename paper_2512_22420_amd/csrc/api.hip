@@ -125,6 +125,12 @@ bool fold_norms(const nj_model_desc& d, int M) {
   return producer_ok(HD) && producer_ok(d.ffn_dim);
 }
 
+// Sums of squares of the folded norm: 128 columns each, or 16 at windows that
+// the small-window GEMM takes (which any workspace may serve).
+size_t ssq_bytes(const nj_model_desc& d, size_t M) {
+  return std::max(M * ((d.d_model + 127) / 128), std::min<size_t>(M, 16 * kSmallMaxTiles) * ((d.d_model + 15) / 16)) * 4;
+}
+
 Layout layout(const nj_model_desc& d, int B, int k) {
   const size_t e = d.dtype == NJ_BF16 ? 2 : 4;
   const size_t T = k + 1, M = (size_t)B * T;
@@ -155,8 +161,8 @@ Layout layout(const nj_model_desc& d, int B, int k) {
   }
   L.h = take(M * d.d_model * 4);
   L.x = take(M * d.d_model * e);
-  L.ssq = take(M * ((d.d_model + 127) / 128) * 4);  // per-row sums of h^2 over 128-column tiles (folded norm)
-  L.rope_cs = take(M * 64 * 2 * 4);                  // the step's RoPE (cos, sin) table (bf16 path)
+  L.ssq = take(ssq_bytes(d, M));        // per-row sums of h^2 over column segments (folded norm)
+  L.rope_cs = take(M * 64 * 2 * 4);     // the step's RoPE (cos, sin) table (bf16 path)
   L.qkv = take(M * qkv * 4);
   L.q = take(M * HD * e);
   L.win_layer_bytes = (size_t)B * d.n_kv_heads * 16 * d.head_dim * e;
@@ -196,7 +202,7 @@ PreLayout pre_layout(const nj_model_desc& d, int B, int k) {
   L.err = take(kAlign);
   L.gemm_cnt = take(kGemmCounterBytes);
   L.x = take(M * d.d_model * e);
-  L.ssq = take(M * ((d.d_model + 127) / 128) * 4);
+  L.ssq = take(ssq_bytes(d, M));
   L.rope_cs = take(M * 64 * 2 * 4);
   L.qkv = take(M * QKV * 4);
   size_t part = d.dtype == NJ_BF16 ? gemm_plan((int)M, QKV, d.d_model, kEpiQkvRope).part_bytes : 0;
@@ -433,17 +439,24 @@ int verify_impl(const nj_model_desc* desc, const nj_weights* w, const nj_kv_cach
   bool fused = fold_norms(d, M) && aligned16(w->final_norm);
   for (int l = 0; l < d.n_layers && fused; ++l)
     fused = aligned16(w->layers[l].attn_norm) && aligned16(w->layers[l].ffn_norm);
-  // Without the folded norm, the input of each GEMM that runs on the
-  // LDS-tiled kernel is written k-blocked by its producer (norm, attention,
-  // SwiGLU epilogue), so the tile loads read 1 KB contiguous units.
-  const bool kb_qkv = bf && !gemm_streams(M, QKV, d.d_model, kEpiQkvRope);
-  const bool kb_o = bf && !gemm_streams(M, d.d_model, HD, kEpiResidual);
-  const bool kb_gu = bf && !gemm_streams(M, F2, d.d_model, kEpiSwiglu);
-  const bool kb_dn = bf && d.ffn_dim % 32 == 0 && !gemm_streams(M, d.d_model, d.ffn_dim, kEpiResidual);
-  const bool kb_lm = bf && !gemm_streams(M, d.vocab, d.d_model, kEpiStore);
+  // The input of each GEMM that runs on the LDS-tiled kernel is written
+  // k-blocked by its producer (norm, attention, SwiGLU epilogue), so the tile
+  // loads read 1 KB contiguous units; with the folded norm, so is that of each
+  // small-window GEMM, whose fragments are then contiguous.
+  auto kblocked = [&](int N, int K, int epi) {
+    return bf && (fused ? gemm_wants_kblocked(M, N, K, epi) : !gemm_streams(M, N, K, epi));
+  };
+  const bool kb_qkv = kblocked(QKV, d.d_model, kEpiQkvRope);
+  const int epi_res = fused ? kEpiResidualNorm : kEpiResidual;
+  const bool kb_o = kblocked(d.d_model, HD, epi_res);
+  const bool kb_gu = kblocked(F2, d.d_model, kEpiSwiglu);
+  const bool kb_dn = d.ffn_dim % 32 == 0 && kblocked(d.d_model, d.ffn_dim, epi_res);
+  const bool kb_lm = kblocked(d.vocab, d.d_model, kEpiStore);
   float* ssq = reinterpret_cast<float*>(ws + L.ssq);
   const int nt = (d.d_model + 127) / 128;
-  const GemmNorm scale_in{ssq, nt, d.rms_eps, nullptr, nullptr, nullptr, nullptr};
+  // the row scale's sums of squares come from the embedding, the O or the down GEMM
+  const int nt_o = gemm_ssq_segments(M, d.d_model, HD), nt_dn = gemm_ssq_segments(M, d.d_model, d.ffn_dim);
+  auto scale_in = [&](int segs) { return GemmNorm{ssq, segs, d.rms_eps, nullptr, nullptr, nullptr, nullptr}; };
 
   // the embedding kernel carries one more workgroup that builds the
   // attention's work list for every layer of the step (bf16)
@@ -455,7 +468,7 @@ int verify_impl(const nj_model_desc* desc, const nj_weights* w, const nj_kv_cach
   const bool rope_in_qkv = !fused && bf && gemm_streams(M, QKV, d.d_model, kEpiQkvRope);
   if (fused)
     NJ_TRY(NJ_PROF_EMBED, launch_embed_gather(last_tokens, draft_tokens, B, T, w->embed, w->layers[0].attn_norm, h, x, ssq, d.d_model,
-                               d.vocab, err, context_lens, d.rope_theta, reinterpret_cast<float*>(ws + L.rope_cs), s, pl),
+                               d.vocab, err, context_lens, d.rope_theta, reinterpret_cast<float*>(ws + L.rope_cs), s, pl, kb_qkv),
            "embed");
   else
     NJ_TRY(NJ_PROF_EMBED, launch_embed_norm(dt, last_tokens, draft_tokens, B, T, w->embed, w->layers[0].attn_norm, h, x, d.d_model,
@@ -471,7 +484,8 @@ int verify_impl(const nj_model_desc* desc, const nj_weights* w, const nj_kv_cach
     if (fused) {  // RoPE and the window store in the QKV GEMM's epilogue
       const QkvRope rope{context_lens, T, d.n_heads, d.n_kv_heads, reinterpret_cast<const float*>(ws + L.rope_cs), q,
                          wk, wv, snap, acnt};
-      NJ_TRY(NJ_PROF_QKV, launch_gemm_norm(x, lw.w_qkv, qkv, M, QKV, d.d_model, kEpiQkvRope, scale_in, gcnt, gpart, s, &rope),
+      NJ_TRY(NJ_PROF_QKV, launch_gemm_norm(x, lw.w_qkv, qkv, M, QKV, d.d_model, kEpiQkvRope, scale_in(l == 0 ? nt : nt_dn), gcnt, gpart, s,
+                                           &rope, kb_qkv),
              "qkv gemm");
     } else {
       if (l > 0) NJ_TRY(NJ_PROF_NORM, launch_rmsnorm(dt, h, lw.attn_norm, x, M, d.d_model, d.rms_eps, s, kb_qkv), "attn_norm");
@@ -500,7 +514,7 @@ int verify_impl(const nj_model_desc* desc, const nj_weights* w, const nj_kv_cach
       const GemmNorm to_ffn{nullptr, 0, 0.f, lw.ffn_norm, x, ssq, nullptr, kb_gu};
       NJ_TRY(NJ_PROF_O, launch_gemm_norm(o, lw.w_o, h, M, d.d_model, HD, kEpiResidualNorm, to_ffn, gcnt, gpart, s, nullptr, kb_o),
              "o gemm");
-      NJ_TRY(NJ_PROF_GATE_UP, launch_gemm_norm(x, lw.w_gate_up, act, M, F2, d.d_model, kEpiSwiglu, scale_in, gcnt, gpart, s,
+      NJ_TRY(NJ_PROF_GATE_UP, launch_gemm_norm(x, lw.w_gate_up, act, M, F2, d.d_model, kEpiSwiglu, scale_in(nt_o), gcnt, gpart, s,
                                                nullptr, kb_gu, kb_dn),
              "gate_up gemm");
       const GemmNorm to_next{nullptr, 0, 0.f, g_next, x, ssq, nullptr, l + 1 < d.n_layers ? kb_qkv : kb_lm};
@@ -519,7 +533,7 @@ int verify_impl(const nj_model_desc* desc, const nj_weights* w, const nj_kv_cach
   bool stats_ready = false;
   float* stats = accept_stats_ptr(ws + L.stats);
   if (fused) {
-    const GemmNorm lm{ssq, nt, d.rms_eps, nullptr, nullptr, nullptr, stats};
+    const GemmNorm lm{ssq, nt_dn, d.rms_eps, nullptr, nullptr, nullptr, stats};
     NJ_TRY(NJ_PROF_LM_HEAD, launch_gemm_norm(x, w->lm_head, logits, M, d.vocab, d.d_model, kEpiLogits, lm, gcnt, gpart, s,
                                              nullptr, kb_lm),
            "lm_head gemm");
@@ -734,11 +748,12 @@ int nightjar_rmsnorm_rope(const nj_model_desc* desc, const float* h, const void*
   float* cs = reinterpret_cast<float*>(ws + L.rope_cs);
   hipError_t e;
   if (fold_norms(d, M)) {  // the step's kernels for this window: norm folded into the QKV GEMM, RoPE in its epilogue
-    e = launch_norm_inputs(h, B, T, attn_norm, ws + L.x, ssq, d.d_model, context_lens, d.rope_theta, cs, s);
+    const bool kb = gemm_wants_kblocked(M, QKV, d.d_model, kEpiQkvRope);
+    e = launch_norm_inputs(h, B, T, attn_norm, ws + L.x, ssq, d.d_model, context_lens, d.rope_theta, cs, s, kb);
     if (e != hipSuccess) return hip_fail(e, "rmsnorm_rope: norm inputs");
     const GemmNorm scale_in{ssq, (d.d_model + 127) / 128, d.rms_eps, nullptr, nullptr, nullptr, nullptr};
     const QkvRope rope{context_lens, T, d.n_heads, d.n_kv_heads, cs, q_out, win_k, win_v, nullptr, nullptr};
-    e = launch_gemm_norm(ws + L.x, w_qkv, ws + L.qkv, M, QKV, d.d_model, kEpiQkvRope, scale_in, gcnt, gpart, s, &rope);
+    e = launch_gemm_norm(ws + L.x, w_qkv, ws + L.qkv, M, QKV, d.d_model, kEpiQkvRope, scale_in, gcnt, gpart, s, &rope, kb);
     return e == hipSuccess ? NJ_OK : hip_fail(e, "rmsnorm_rope: qkv gemm");
   }
   const bool kb = bf && !gemm_streams(M, QKV, d.d_model, kEpiQkvRope);

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kNormThreads) void embed_gather_kernel(
     const int32_t* __restrict__ last, const int32_t* __restrict__ drafts, int T_, const bf16_t* __restrict__ embed,
     const bf16_t* __restrict__ gain, float* __restrict__ h, bf16_t* __restrict__ x, float* __restrict__ ssq, int d,
     int V, int* __restrict__ err, const int32_t* __restrict__ ctx, RopeFreqHead f, float* __restrict__ rope_cs,
-    const float* __restrict__ hin, AttnPlan plan) {
+    const float* __restrict__ hin, int kbM, AttnPlan plan) {
   // the extra workgroup (dispatched first, so it overlaps the rows): the
   // attention's work list
   if (plan.work && blockIdx.x == 0) {
@@ -188,7 +188,8 @@ __global__ __launch_bounds__(kNormThreads) void embed_gather_kernel(
       if (!hin) store4(h + (size_t)row * d + j, hv[it]);
 #pragma unroll
       for (int q = 0; q < 4; ++q) o[q] = hv[it][q] * gv[it][q];
-      store4(x + (size_t)row * d + j, o);
+      // row-major, or k-blocked [d/32][M][32]
+      store4(kbM ? x + ((size_t)(j >> 5) * kbM + row) * 32 + (j & 31) : x + (size_t)row * d + j, o);
       part = hv[it][0] * hv[it][0];
       part = fmaf(hv[it][1], hv[it][1], part);
       part = fmaf(hv[it][2], hv[it][2], part);
@@ -449,23 +450,24 @@ hipError_t launch_embed_norm(int dtype, const int32_t* last, const int32_t* draf
 
 hipError_t launch_embed_gather(const int32_t* last, const int32_t* drafts, int B, int T, const void* embed,
                                const void* gain, float* h, void* x, float* ssq, int d, int V, int* err,
-                               const int32_t* ctx, float theta, float* rope_cs, hipStream_t s, const AttnPlan* plan) {
+                               const int32_t* ctx, float theta, float* rope_cs, hipStream_t s, const AttnPlan* plan,
+                               bool x_kblocked) {
   RopeFreqHead f{};
   for (int j = 0; j < 64; ++j) f.inv_freq[j] = pow((double)theta, -2.0 * j / 128);
   const AttnPlan pl = plan ? *plan : AttnPlan{};
   hipLaunchKernelGGL(embed_gather_kernel, dim3(B * T + (pl.work ? 1 : 0)), dim3(kNormThreads), 0, s, last, drafts, T,
                      static_cast<const bf16_t*>(embed), static_cast<const bf16_t*>(gain), h, static_cast<bf16_t*>(x),
-                     ssq, d, V, err, ctx, f, rope_cs, nullptr, pl);
+                     ssq, d, V, err, ctx, f, rope_cs, nullptr, x_kblocked ? B * T : 0, pl);
   return hipGetLastError();
 }
 
 hipError_t launch_norm_inputs(const float* h, int B, int T, const void* gain, void* x, float* ssq, int d,
-                              const int32_t* ctx, float theta, float* rope_cs, hipStream_t s) {
+                              const int32_t* ctx, float theta, float* rope_cs, hipStream_t s, bool x_kblocked) {
   RopeFreqHead f{};
   for (int j = 0; j < 64; ++j) f.inv_freq[j] = pow((double)theta, -2.0 * j / 128);
   hipLaunchKernelGGL(embed_gather_kernel, dim3(B * T), dim3(kNormThreads), 0, s, nullptr, nullptr, T, nullptr,
                      static_cast<const bf16_t*>(gain), nullptr, static_cast<bf16_t*>(x), ssq, d, 0, nullptr, ctx, f,
-                     rope_cs, h, AttnPlan{});
+                     rope_cs, h, x_kblocked ? B * T : 0, AttnPlan{});
   return hipGetLastError();
 }
 

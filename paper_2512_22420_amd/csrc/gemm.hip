@@ -224,16 +224,19 @@ __global__ __launch_bounds__(kNW * 64) void gemm_stream_kernel(GemmK a) {
 
   // Loads only the epilogue needs are issued first, so that they complete
   // under the weight stream instead of adding a round trip at either end.
-  // Input-side norm: this thread's 8 sums-of-squares partials (8 lanes per
-  // row; lane c takes partials c, c+8, ...).
+  // Input-side norm: this thread's sums-of-squares partials (LPR lanes per
+  // row; lane c takes partials c, c+LPR, ...): up to 64 per row (128 columns
+  // each), or up to 256 at windows that the small-window kernel may have
+  // produced (16 columns each).
   __shared__ float s_rinv[ROWS];
-  const bool scaled = a.ssq_in != nullptr;
-  float ssq_v[8];
+  const bool scaled = EPI != kEpiResidual && EPI != kEpiResidualNorm && a.ssq_in != nullptr;
+  constexpr int LPR = MT == 1 ? 32 : MT == 2 ? 16 : 8, SQ = (MT <= kSmallMaxTiles ? kMaxSsqSegments : 64) / LPR;
+  float ssq_v[SQ];
   if (scaled) {
-    const int row = min((int)threadIdx.x / 8, ROWS - 1), c = threadIdx.x % 8;
+    const int row = min((int)threadIdx.x / LPR, ROWS - 1), c = threadIdx.x % LPR;
     const float* sp = a.ssq_in + (size_t)min(m0 + row, M - 1) * a.nt_in;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) ssq_v[j] = c + 8 * j < a.nt_in ? sp[c + 8 * j] : 0.f;
+    for (int j = 0; j < SQ; ++j) ssq_v[j] = c + LPR * j < a.nt_in ? sp[c + LPR * j] : 0.f;
   }
   // QKV + RoPE epilogue: the (cos, sin) of this thread's rotation units
   // (unit u = thread + it * NTH: row u / 64, pair u % 64).
@@ -393,15 +396,14 @@ __global__ __launch_bounds__(kNW * 64) void gemm_stream_kernel(GemmK a) {
   }
 
   if (scaled) {
-    // 1/rms of this workgroup's rows: lane sums in order, a 3-step butterfly
-    // over the row's 8 lanes (LDS is free: the loop ended on a barrier)
+    // 1/rms of this workgroup's rows: lane sums in order, a butterfly over the
+    // row's lanes (LDS is free: the loop ended on a barrier)
     float t = 0.f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) t += ssq_v[j];
-    t += __shfl_xor(t, 1);
-    t += __shfl_xor(t, 2);
-    t += __shfl_xor(t, 4);
-    if (threadIdx.x % 8 == 0 && (int)threadIdx.x / 8 < ROWS) s_rinv[threadIdx.x / 8] = 1.0f / sqrtf(t / (float)K + a.eps);
+    for (int j = 0; j < SQ; ++j) t += ssq_v[j];
+#pragma unroll
+    for (int o = 1; o < LPR; o <<= 1) t += __shfl_xor(t, o);
+    if (threadIdx.x % LPR == 0 && (int)threadIdx.x / LPR < ROWS) s_rinv[threadIdx.x / LPR] = 1.0f / sqrtf(t / (float)K + a.eps);
     __syncthreads();
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[mt] *= s_rinv[mt * 16 + r];
@@ -628,7 +630,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_logits_kernel(GemmK a) {
   constexpr int CPG = TPW * 16 / kStatChunk;  // statistics chunks per group
   static_assert(CPG * kStatChunk == TPW * 16, "a group's columns are whole statistics chunks");
   constexpr int ROWS = MT * 16, NTH = NW * 64;
-  static_assert(ROWS * 8 <= NTH, "one pass of sum-of-squares lanes");
   constexpr int CH = ROWS * (kSK / 8), PT = (CH + NTH - 1) / NTH;
   constexpr int OS = TPW * 16 + 4;  // LDS row stride of an output tile, in floats
   __shared__ __attribute__((aligned(16))) bf16_t xs[2][ROWS * kXStride];
@@ -654,21 +655,25 @@ __global__ __launch_bounds__(NW * 64) void gemm_logits_kernel(GemmK a) {
     xo[c] = row * kXStride + col;
   }
   const bool scaled = a.ssq_in != nullptr;
-  float ssq_v[8];
+  // up to 64 sums of squares per row (128 columns each) over 8 lanes, or, at
+  // windows that the small-window kernel may have produced, up to 256 (16
+  // columns each) over as many lanes as the workgroup has per row
+  constexpr int LPR = MT > kSmallMaxTiles ? 8 : 32, SQ = (MT > kSmallMaxTiles ? 64 : kMaxSsqSegments) / LPR;
+  static_assert(ROWS * LPR <= NTH, "one pass of sum-of-squares lanes");
+  float ssq_v[SQ];
   if (scaled) {
-    const int row = min((int)threadIdx.x / 8, ROWS - 1), c = threadIdx.x % 8;
+    const int row = min((int)threadIdx.x / LPR, ROWS - 1), c = threadIdx.x % LPR;
     const float* sp = a.ssq_in + (size_t)min(row, M - 1) * a.nt_in;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) ssq_v[j] = c + 8 * j < a.nt_in ? sp[c + 8 * j] : 0.f;
+    for (int j = 0; j < SQ; ++j) ssq_v[j] = c + LPR * j < a.nt_in ? sp[c + LPR * j] : 0.f;
   }
   auto row_scales = [&] {  // 1/rms of every row into s_rinv
     float t = 0.f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) t += ssq_v[j];
-    t += __shfl_xor(t, 1);
-    t += __shfl_xor(t, 2);
-    t += __shfl_xor(t, 4);
-    if (threadIdx.x % 8 == 0 && (int)threadIdx.x / 8 < ROWS) s_rinv[threadIdx.x / 8] = 1.0f / sqrtf(t / (float)K + a.eps);
+    for (int j = 0; j < SQ; ++j) t += ssq_v[j];
+#pragma unroll
+    for (int o = 1; o < LPR; o <<= 1) t += __shfl_xor(t, o);
+    if (threadIdx.x % LPR == 0 && (int)threadIdx.x / LPR < ROWS) s_rinv[threadIdx.x / LPR] = 1.0f / sqrtf(t / (float)K + a.eps);
     __syncthreads();
   };
   // Windows of more than 64 rows have no registers to spare for the partials
@@ -1070,7 +1075,49 @@ GemmPlan gemm_logits_widen(const GemmPlan& p, int M, int N) {
 }
 
 namespace {
+// Windows of up to 32 rows whose GEMM the small-window kernel runs faster (both
+// kernels measured, us, streaming -> small; 8B, 7B and 1B layer shapes):
+// - residual GEMMs (O, down) of one row tile: 8B 12.0 -> 8.0 and 23.2 -> 20.3,
+//   7B 15.3 -> 7.4 and 26.8 -> 24.9, 1B 10.4 -> 4.8 and 12.8 -> 10.5.  Each
+//   workgroup reads all of x for its 16 columns, so at two row tiles it only
+//   pays with k-blocked x (the step's, kEpiResidualNorm) and up to 4096 k (8B O
+//   13.7 -> 10.7; 8B down 25 -> 29);
+// - QKV with RoPE: 8B 14.1 -> 12.0 and, two row tiles, 15.9 -> 14.9 (three: 17.7
+//   -> 18.4), 7B 16.3 -> 10.0, 1B 11.5 -> 7.8;
+// - gate/up of one row tile (two: 8B 37 -> 48), unless the streaming kernel
+//   fills the CUs evenly in whole rounds without splitting K, which already
+//   runs at the read rate (8B, 224 workgroups: 36 against 40; 7B, 296
+//   workgroups: 54.6 -> 42.2; 1B, split K: 16.9 -> 13.6).
+bool small_wins(int M, int N, int K, int epi) {
+  const int mt = (M + 15) / 16;
+  if (mt > kSmallMaxTiles || K % 32) return false;
+  switch (epi) {
+    case kEpiResidual: return N / 16 <= kMaxSsqSegments && mt == 1;
+    case kEpiResidualNorm: return N / 16 <= kMaxSsqSegments && (mt == 1 || K <= 4096);
+    case kEpiQkvRope: return N % 128 == 0 && mt <= 2;
+    case kEpiSwiglu: {
+      if (mt > 1) return false;
+      const GemmPlan p = gemm_stream_plan(M, N, K, epi, 0, 1);
+      const int rounds = (p.ntiles + 255) / 256;
+      return p.nkc > 1 || rounds * 256 * 5 > p.ntiles * 6;
+    }
+    default: return false;
+  }
+}
+
 GemmPlan gemm_plan_uncached(int M, int N, int K, int epi) {
+  if (small_wins(M, N, K, epi)) {
+    GemmPlan p{};
+    p.tile = kTileNone;
+    p.small = 1;
+    p.mt = (M + 15) / 16;
+    p.ntiles = epi == kEpiQkvRope ? N / 32 : epi == kEpiSwiglu ? N / 32 : N / 16;
+    p.mblocks = p.nkc = p.depth = 1;
+    // 16 waves where fewer workgroups than CUs have long sums (8B QKV at 16 rows 12.8 -> 12.1 us; else no gain)
+    p.nw = epi == kEpiQkvRope && p.ntiles < 256 && K >= 4096 ? 16 : 8;
+    return p;
+  }
+  if (epi == kEpiResidualNorm) epi = kEpiResidual;
   if (M >= kTileMinRows && tile_fits(M, N, K)) {
     // wide fp32-store GEMMs (the LM head) of up to 96 rows: the persistent
     // kernel reads the weights once and runs ~10% ahead of the best tile
@@ -1145,7 +1192,11 @@ hipError_t launch_gemm_plan(const void* x, const void* w, void* y, int M, int N,
                             int* counters, float* part, hipStream_t s, bool x_kblocked, bool y_kblocked) {
   if (p.tile != kTileNone)
     return launch_gemm_tile(x, w, y, M, N, K, epi, p, counters, part, s, nullptr, x_kblocked, y_kblocked);
+  if (p.small && (epi == kEpiResidual || epi == kEpiSwiglu))
+    return launch_gemm_small(x, w, y, M, N, K, epi, p, nullptr, nullptr, s, x_kblocked, y_kblocked);
   if (x_kblocked) return hipErrorInvalidValue;  // the streaming kernel reads row-major x
+  if (p.small)  // an epilogue it has not got (the QKV projection without RoPE): streamed, without a split of K
+    return launch_gemm_plan(x, w, y, M, N, K, epi, gemm_stream_plan(M, N, K, epi, 1, 1), counters, part, s, false, y_kblocked);
   const int Nout = (epi == kEpiSwiglu) ? N / 2 : N;
   GemmK a{static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), y, p.nkc > 1 ? part : nullptr,
           p.nkc > 1 ? counters : nullptr, M, Nout, K, K / 32, p.stages_per_chunk, (int)p.part_bytes, nullptr, 0, nullptr, 0, 0.f, nullptr, nullptr, nullptr, {},
@@ -1168,6 +1219,15 @@ hipError_t launch_gemm_logits(const void* x, const void* w, float* y, float* sta
   return launch_logits(a, p, s);
 }
 
+int gemm_ssq_segments(int M, int N, int K) {
+  return gemm_plan(M, N, K, kEpiResidualNorm).small ? N / 16 : (N + 127) / 128;
+}
+
+bool gemm_wants_kblocked(int M, int N, int K, int epi) {
+  const GemmPlan p = gemm_plan(M, N, K, epi);
+  return p.tile != kTileNone || p.small;
+}
+
 bool gemm_streams(int M, int N, int K, int epi) { return gemm_plan(M, N, K, epi).tile == kTileNone; }
 
 int logits_stat_entries(int M, int N, int K) {
@@ -1181,7 +1241,7 @@ hipError_t launch_gemm_norm(const void* x, const void* w, void* y, int M, int N,
                             int* counters, float* part, hipStream_t s, const QkvRope* rope, bool x_kblocked,
                             bool y_kblocked) {
   const int pe = epi == kEpiResidualNorm ? kEpiResidual : epi == kEpiLogits ? kEpiStore : epi;
-  const GemmPlan p = gemm_plan(M, N, K, epi == kEpiQkvRope ? kEpiQkvRope : pe);
+  const GemmPlan p = gemm_plan(M, N, K, epi == kEpiLogits ? kEpiStore : epi);
   if (p.tile != kTileNone) {
     // the tiled kernel: the row scale in every epilogue, the next norm's
     // inputs from the slice-reduced residual epilogue (it checks the plan);
@@ -1190,6 +1250,7 @@ hipError_t launch_gemm_norm(const void* x, const void* w, void* y, int M, int N,
     return launch_gemm_tile(x, w, y, M, N, K, pe, p, counters, part, s, epi == kEpiLogits ? nm.stats : nullptr,
                             x_kblocked, y_kblocked, &nm);
   }
+  if (p.small) return launch_gemm_small(x, w, y, M, N, K, epi, p, &nm, rope, s, x_kblocked, y_kblocked);
   if (x_kblocked) return hipErrorInvalidValue;  // the streaming kernel reads row-major x
   const int Nout = (epi == kEpiSwiglu) ? N / 2 : N;
   GemmK a{static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), y, p.nkc > 1 ? part : nullptr,

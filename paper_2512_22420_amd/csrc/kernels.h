@@ -32,6 +32,7 @@ struct GemmPlan {
   int mt, nw, ntiles, mblocks, nkc, stages_per_chunk;
   int depth;  // streaming kernel: weight stages in flight ahead of the one being multiplied (1 or 3)
   size_t part_bytes, counter_bytes;
+  int small;  // the small-window kernel (gemm_small.hip; mt row tiles, nw waves), else 0
   int grid;   // tiled kernel: workgroups of the stream-K schedule
   int key_m, key_n, key_k, key_epi;  // the arguments gemm_plan chose it for (its plan table checks them)
   // tiled kernel, one-segment split plans on at most kParMaxGrid workgroups:
@@ -52,7 +53,8 @@ unsigned split_foreign_mask();
 // CUs of the current device (queried once; 0 when there is no device).
 int device_cus();
 // The plan the bf16 GEMM runs for y = x . w^T with epilogue epi; epi =
-// kEpiQkvRope plans the QKV projection (store output), for which a
+// kEpiResidualNorm plans a residual GEMM of the step with folded norms (its x
+// comes k-blocked where the plan wants it), kEpiQkvRope plans the QKV projection (store output), for which a
 // streaming plan also applies RoPE while a tiled one needs the RoPE kernel.
 // Plans of the same arguments are computed once and kept.
 GemmPlan gemm_plan(int M, int N, int K, int epi);
@@ -159,8 +161,22 @@ struct QkvRope {
   int32_t* ctx_snap;
   int* attn_cnt;
 };
-// Whether gemm_plan picks the weight-streaming kernel for this shape (the
-// only one with the folded norm).
+// The small-window kernel alone (p.small; residual, residual + norm, SwiGLU and
+// QKV + RoPE epilogues).  With the residual + norm epilogue its
+// sums of squares cover 16 columns each (gemm_ssq_segments).
+constexpr int kSmallMaxTiles = 2;  // 16-row tiles of the largest window it takes
+constexpr int kMaxSsqSegments = 256;  // sums of squares per row that the weight-streaming kernels read, at most
+hipError_t launch_gemm_small(const void* x, const void* w, void* y, int M, int N, int K, int epi, const GemmPlan& p,
+                             const GemmNorm* nm, const QkvRope* rope, hipStream_t s, bool x_kblocked = false,
+                             bool y_kblocked = false);
+// Sums of squares per row that the residual + norm GEMM of this shape writes
+// (the nt_in of the GEMM that consumes them).
+int gemm_ssq_segments(int M, int N, int K);
+// Whether the plan's kernel reads its x best k-blocked (the LDS-tiled and the
+// small-window kernel).
+bool gemm_wants_kblocked(int M, int N, int K, int epi);
+// Whether gemm_plan picks a weight-streaming kernel for this shape (it reads
+// row-major x; the small-window kernel, which reads either, counts as one).
 bool gemm_streams(int M, int N, int K, int epi);
 // (max, sum of exp) pairs per row that the LM-head GEMM's statistics epilogue
 // writes: one per 128-column chunk, per persistent workgroup, or per column tile
@@ -199,12 +215,12 @@ hipError_t launch_embed_norm(int dtype, const int32_t* last, const int32_t* draf
 hipError_t launch_embed_gather(const int32_t* last, const int32_t* drafts, int B, int T, const void* embed,
                                const void* gain, float* h, void* x, float* ssq, int d, int V, int* err,
                                const int32_t* ctx, float theta, float* rope_cs, hipStream_t s,
-                               const AttnPlan* plan = nullptr);
+                               const AttnPlan* plan = nullptr, bool x_kblocked = false);
 
 // The same outputs (x, ssq, rope_cs) for given residual rows h [B*T][d] fp32
 // instead of embedding rows (h is only read).
 hipError_t launch_norm_inputs(const float* h, int B, int T, const void* gain, void* x, float* ssq, int d,
-                              const int32_t* ctx, float theta, float* rope_cs, hipStream_t s);
+                              const int32_t* ctx, float theta, float* rope_cs, hipStream_t s, bool x_kblocked = false);
 
 // x[r] = rmsnorm(h[r]) * gain; x row-major, or k-blocked (as launch_gemm_tile reads it)
 hipError_t launch_rmsnorm(int dtype, const float* h, const void* gain, void* x, int M, int d, float eps,

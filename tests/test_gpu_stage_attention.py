@@ -192,8 +192,14 @@ def _pre_case(shape, B, k, seed):
     (L8, [1024] * 8, 5),                                # 48 rows, the headline window
     (L8, list(range(0, 64 * 31, 31)), 5),               # 384 rows: norm kernel, tiled GEMM, RoPE kernel
     (QW, [4000, 3, 1500], 7),                           # Qwen layout (d 3584, G 7), theta 1e6
+    (L8, [77], 0),                                      # small-window kernel: one row,
+    (L8, [5, 900], 7),                                  # 16 rows, one tile full,
+    (QW, [12], 15),                                     # every slot of a window block used,
+    (L8, [3, 100, 2000, 40], 7),                        # 32 rows, two tiles full,
+    (L8, [9] * 11, 2),                                  # 33 rows: the streaming kernel's first
     (TF, [32, 48], 3),                                  # fp32 path
-], ids=["8b-18rows", "8b-48rows", "8b-384rows", "qwen-24rows", "f32"])
+], ids=["8b-18rows", "8b-48rows", "8b-384rows", "qwen-24rows", "8b-1row", "8b-16rows", "qwen-16rows", "8b-32rows",
+        "8b-33rows", "f32"])
 def test_rmsnorm_rope_matches_oracle(shape, ctx, k):
     ctx = np.asarray(ctx, np.int32)
     B, T = len(ctx), k + 1

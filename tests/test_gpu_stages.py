@@ -82,6 +82,25 @@ def test_gemm_bf16_swiglu(M, F, K):
     assert np.abs(got - ref).max() <= 2 ** -8 * np.abs(ref).max() + 1e-6
 
 
+@pytest.mark.parametrize("M", [1, 5, 15, 16, 17])  # one row tile, its edges, and the streaming kernel's first
+@pytest.mark.parametrize("N,K", [(16, 32), (48, 96), (272, 800), (2048, 2048), (3584, 3584), (4112, 512)])
+@pytest.mark.parametrize("epi", [nb.NJ_GEMM_RESIDUAL, nb.NJ_GEMM_SWIGLU], ids=["residual", "swiglu"])
+def test_gemm_small_windows(M, N, K, epi):
+    """K split over a workgroup's waves: fewer k-steps than waves, ragged
+    shares and stages, every row count's edge, and N past the small kernel's
+    residual limit (4112)."""
+    rng = np.random.default_rng(M * 31 + N + K)
+    rows = 2 * N if epi == nb.NJ_GEMM_SWIGLU else N
+    x = W.f32_to_bf16_bits(rng.standard_normal((M, K), dtype=np.float32))
+    w = W.f32_to_bf16_bits(rng.standard_normal((rows, K), dtype=np.float32) * 0.03)
+    y0 = rng.standard_normal((M, N), dtype=np.float32)
+    y = _dev(y0.copy()) if epi == nb.NJ_GEMM_RESIDUAL else torch.empty((M, N), dtype=torch.int16, device="cuda")
+    dx, dw = _dev(x), _devw(w)
+    _gemm(nb.NJ_BF16, dx, dw, y, M, rows, K, epi)
+    ref = _gemm_ref(x, w, epi, y0)
+    assert np.abs(_gemm_out(y, epi) - ref).max() <= _gemm_tol(ref, epi)
+
+
 def _gemm_ref(x, w, epi, y0=None):
     acc = oracle.widen(x, "bf16") @ oracle.widen(w, "bf16").T
     if epi == nb.NJ_GEMM_STORE:
