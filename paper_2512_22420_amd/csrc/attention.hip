@@ -29,6 +29,7 @@ namespace nj {
 namespace {
 
 constexpr int kD = 128;  // head dim of the bf16 path
+constexpr size_t kStreamBytes = (size_t)128 << 20;
 constexpr int kAttnWgsPerCu = 2;  // resident attention workgroups per CU (registers, LDS of the larger forms)
 
 __device__ __forceinline__ bf16x8 ld8(const bf16_t* p) {
@@ -190,8 +191,10 @@ __device__ __forceinline__ bf16x8 softmax_step(const float (&st)[8], float scale
 }
 
 typedef const __attribute__((address_space(1))) char* gptr;
+template <bool STREAM>
 __device__ __forceinline__ bf16x8 gld8(gptr p) {
-  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(p));
+  const auto q = reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(p);
+  return __builtin_bit_cast(bf16x8, STREAM ? __builtin_nontemporal_load(q) : *q);
 }
 
 // Up to 32 query rows (RT = 1 or 2 row tiles).  Each wave takes its own pairs
@@ -202,10 +205,9 @@ __device__ __forceinline__ bf16x8 gld8(gptr p) {
 // loads in flight set the rate (16 to 32 KB per wave, two waves per SIMD); at
 // few blocks per split the chain of dependent accesses (item, page ids,
 // blocks, merge) does.  Against the LDS kernel of four-block chunks with
-// masks and exec changes in its inner loop: 8 sequences of 1024 tokens at 24
-// rows 17.5 -> 13.8 us and at 2 rows (16 heads) 15.7 -> 13.3 us, 64 sequences of
-// ~870 tokens at 20 rows 54.7 -> 50.5 us; 256 sequences of 2400 tokens at 7 rows
-// 214 us, 5.9 TB/s.
+// masks and exec changes in its inner loop (cacheable loads): 8 sequences of
+// 1024 tokens at 24 rows 17.5 -> 13.8 us and at 2 rows (8 KV heads) 15.7 -> 13.3
+// us, 64 sequences of ~870 tokens at 20 rows 54.7 -> 50.5 us.
 //
 // A pair is 32 tokens: MFMA h of the score product takes, as row r of its A
 // operand, token 8 ((r >> 2) & 1) + 4 h + (r & 3) of block r >> 3, so the lane
@@ -214,7 +216,7 @@ __device__ __forceinline__ bf16x8 gld8(gptr p) {
 // of a 16x16x32 MFMA whose A operand is eight consecutive tokens of one dim of
 // a V block, one 16-byte load.
 constexpr int kRegRow = kD + 4;  // LDS row stride of the wave merge, in floats
-template <int RT>
+template <int RT, bool STREAM>
 __global__ __launch_bounds__(256, 2) void attn_reg_kernel(AttnK a) {
   static_assert(RT == 1 || RT == 2, "one or two row tiles");
   constexpr int NP = 4;  // waves
@@ -285,12 +287,12 @@ __global__ __launch_bounds__(256, 2) void attn_reg_kernel(AttnK a) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) kf[decltype(setc)::value % NS][h * 4 + s] = gld8(kl + h * (4 * kD * 2) + s * 64);
+      for (int s = 0; s < 4; ++s) kf[decltype(setc)::value % NS][h * 4 + s] = gld8<STREAM>(kl + h * (4 * kD * 2) + s * 64);
   };
   auto load_v = [&](auto setc, int j) {
     const gptr vl = page(a.vp, win_v, j, (g & 2) != 0) + vofs;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) vf[decltype(setc)::value % NS][dt] = gld8(vl + dt * (16 * kBlock * 2));
+    for (int dt = 0; dt < 8; ++dt) vf[decltype(setc)::value % NS][dt] = gld8<STREAM>(vl + dt * (16 * kBlock * 2));
   };
 
   float m_run[RT], l_run[RT];
@@ -455,6 +457,7 @@ __global__ __launch_bounds__(256, 2) void attn_reg_kernel(AttnK a) {
 // different); V dim d keeps its two halves swapped when bit 3 of d is set.
 constexpr int kPairBuf = 4;
 constexpr int kPairBytes = 4 * kBlock * kD * 2;  // K of both blocks, then V of both
+template <bool STREAM>
 __global__ __launch_bounds__(256, 2) void attn_lds_kernel(AttnK a) {
   __shared__ __attribute__((aligned(16))) char smem[kPairBuf * kPairBytes];
   const AttnWork item = a.work[blockIdx.x];
@@ -506,9 +509,14 @@ __global__ __launch_bounds__(256, 2) void attn_lds_kernel(AttnK a) {
     const bf16_t* src = id >= 0 ? pages + ((size_t)id * a.Hkv + kvh) * (kBlock * kD) : win;
     const uint32_t dst = lds0 + (uint32_t)((p % kPairBuf) * kPairBytes + wave * (kBlock * kD * 2));
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lofs[i]), "s"(src), "s"(dst + i * 1024)
-                   : "memory", "m0");
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(lofs[i]), "s"(src), "s"(dst + i * 1024)
+                     : "memory", "m0");
+      else
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lofs[i]), "s"(src), "s"(dst + i * 1024)
+                     : "memory", "m0");
+    }
   };
 
   bf16x8 qf[4];
@@ -801,11 +809,23 @@ hipError_t launch_attention(const AttnArgs& x, hipStream_t s) {
           (int)std::min<size_t>(attention_partial_floats(x.B, x.Hkv, x.T, G, kD) / (kD + 2) * 2 * 4, INT32_MAX),
           x.out_kblocked ? x.B * x.T : 0};
   if (!x.work || x.wgs < x.B * x.Hkv || x.wgs > x.B * x.Hkv + kExtraWorkgroups) return hipErrorInvalidValue;
-  dim3 grid(x.wgs);
-  switch (RT) {
-    case 1: hipLaunchKernelGGL(attn_reg_kernel<1>, grid, dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(attn_reg_kernel<2>, grid, dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL(attn_lds_kernel, grid, dim3(256), 0, s, a); break;
+  // A cache read that the last-level cache (256 MB) cannot keep to the next
+  // launch anyway goes non-temporal, which reads faster from HBM (64 sequences of
+  // 4096 tokens 185 -> 165 us, of ~870 tokens 50.3 -> 47.8; 7B shape at 56 rows
+  // 269 -> 248); a small one stays cacheable (8 sequences of 1024 tokens 14.0
+  // against 15.0 us when they come round again).  The host knows the largest
+  // context the table allows, not the contexts.
+  const bool stream = (size_t)x.B * x.max_blocks * x.Hkv * (2 * kBlock * kD * 2) > kStreamBytes;
+  const dim3 grid(x.wgs), block(256);
+  if (RT == 1) {
+    if (stream) hipLaunchKernelGGL((attn_reg_kernel<1, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((attn_reg_kernel<1, false>), grid, block, 0, s, a);
+  } else if (RT == 2) {
+    if (stream) hipLaunchKernelGGL((attn_reg_kernel<2, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((attn_reg_kernel<2, false>), grid, block, 0, s, a);
+  } else {
+    if (stream) hipLaunchKernelGGL(attn_lds_kernel<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(attn_lds_kernel<false>, grid, block, 0, s, a);
   }
   return hipGetLastError();
 }
