@@ -432,7 +432,9 @@ enum {
  * M >= 1; for bf16 K % 32 == 0 and the output width % 16 == 0.  workspace:
  * device, 256-byte aligned, at least nightjar_gemm_workspace_bytes(...) bytes,
  * prepared once with nightjar_workspace_init (split-K counters start at zero
- * and are left at zero by every call).
+ * and are left at zero by every call).  A call may write partial sums and a
+ * k-blocked copy of x into it: calls that overlap in time need workspaces of
+ * their own.
  */
 size_t nightjar_gemm_workspace_bytes(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t epilogue);
 int nightjar_gemm(int32_t dtype, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,

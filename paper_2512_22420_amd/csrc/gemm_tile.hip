@@ -614,7 +614,22 @@ hipError_t launch_shape_any(const TileK& a, int epi, bool one_segment, hipStream
                      : launch_shape<BM, BN, WM, WN, NBUF, true>(a, epi, s);
 }
 
+// x row-major [M][K] to k-blocked [K/32][M][32], K % 64 == 0: a wave copies 4
+// rows x 128 k as 16-byte pieces (256 contiguous bytes of a row read, 256 of a
+// k block written).
+__global__ __launch_bounds__(256) void kblock_kernel(const u32x4* __restrict__ x, u32x4* __restrict__ dst, int M, int K) {
+  const int lane = threadIdx.x & 63, P = K / 8;  // 16-byte pieces per row
+  const int p = blockIdx.x * 16 + (lane & 15), row = (blockIdx.y * 4 + (threadIdx.x >> 6)) * 4 + (lane >> 4);
+  if (p < P && row < M) dst[((size_t)(p >> 2) * M + row) * 4 + (p & 3)] = x[(size_t)row * P + p];
+}
 }  // namespace
+
+hipError_t launch_kblock(const void* x, void* dst, int M, int K, hipStream_t s) {
+  if (K % 64 || M > kKblockMaxRows) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kblock_kernel, dim3((K / 8 + 15) / 16, (M + 15) / 16), dim3(256), 0, s, static_cast<const u32x4*>(x),
+                     static_cast<u32x4*>(dst), M, K);
+  return hipGetLastError();
+}
 
 bool tile_one_segment(const GemmPlan& p, int K) {
   const long tiles = (long)p.ntiles * p.mblocks;

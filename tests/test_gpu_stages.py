@@ -248,6 +248,42 @@ def test_gemm_kblocked_operands_match_row_major(kernel, split, M, N, K, epi):
                           epi | nb.NJ_GEMM_KBLOCKED, nb.NJ_GEMM_STREAM, 0, ws.data_ptr(), nbytes, _stream())
 
 
+@pytest.mark.parametrize("M,N,K,epi", [
+    (256, 1040, 576, nb.NJ_GEMM_STORE),             # first window that copies; K of 4.5 copy blocks, ragged N
+    (257, 1024, 64, nb.NJ_GEMM_RESIDUAL),           # one k step, a row past the copy's 16
+    (301, 512, 2048, nb.NJ_GEMM_STORE),             # split K: the copy lies past counters and partials
+    (97, 2 * 8192, 192, nb.NJ_GEMM_SWIGLU),         # few rows, wide matrix
+    (255, 1024, 512, nb.NJ_GEMM_STORE),             # below the rule: no copy
+])
+def test_gemm_row_major_x_copied_k_blocked(M, N, K, epi):
+    """nightjar_gemm copies a row-major x k-blocked where that pays: the same
+    bytes as without the copy (a workspace with no room for it) and within the
+    tolerance of the reference, and the split counters stay zero."""
+    x, w, y0 = _gemm_case(M, N, K, epi, seed=M + N + K)
+    Nout = N // 2 if epi == nb.NJ_GEMM_SWIGLU else N
+    dx, dw = _dev(x), _devw(w)
+    full = nb.gemm_workspace_bytes(nb.NJ_BF16, M, N, K, epi)
+    least = nb.gemm_plan_workspace_bytes(nb.NJ_BF16, M, N, K, epi, nb.NJ_GEMM_AUTO, 0)
+    assert (full > least) == (M >= 256 or N >= 16384)
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+    nb.workspace_init(ws.data_ptr(), full, _stream())
+    outs = []
+    for nbytes in (full, least, full):
+        if epi == nb.NJ_GEMM_SWIGLU:
+            y = torch.empty((M, Nout), dtype=torch.int16, device="cuda")
+        elif epi == nb.NJ_GEMM_RESIDUAL:
+            y = _dev(y0.copy())
+        else:
+            y = torch.full((M, Nout), float("nan"), dtype=torch.float32, device="cuda")
+        nb.gemm(nb.NJ_BF16, dx.data_ptr(), dw.data_ptr(), y.data_ptr(), M, N, K, epi, ws.data_ptr(), nbytes, _stream())
+        torch.cuda.synchronize()
+        outs.append(y)
+    for o in outs[1:]:
+        assert torch.equal(outs[0].view(torch.uint8), o.view(torch.uint8))
+    ref = _gemm_ref(x, w, epi, y0)
+    assert np.abs(_gemm_out(outs[0], epi) - ref).max() <= _gemm_tol(ref, epi)
+
+
 def test_gemm_lm_head_large_window_sampled():
     """The LM-head shape at the largest window of the large-batch grid (768 rows
     x 128256 x 4096, auto plan), checked on sampled rows and a column band."""
