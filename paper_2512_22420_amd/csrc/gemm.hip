@@ -985,7 +985,11 @@ namespace {
 // shape, K splits of 1..8 (slice-reduced) and a 256-workgroup stream-K grid:
 // the plan chosen is the fastest measured one, or within 3% of it, at 70 of
 // 83 points and within 15% at the others (the sustained fractions below are
-// fitted for ranking plans, so they sit above the measured ones).
+// fitted for ranking plans, so they sit above the measured ones).  The 160x128
+// and 192x128 shapes and the 8-wave 128x128 one, added later, were fitted to
+// the same GEMMs at 65..384 rows (us, without -> with them): 8B gate/up 112
+// rows 56 -> 51, 160 rows 63 -> 60, 8B down 112 rows 39 -> 34, 144 rows 43 ->
+// 39.5, 7B down 144 rows 51 -> 46.6, 8B QKV 160 rows 27.9 -> 26.6.
 // Tiled kernel: rounds of resident workgroups times one tile's MFMA time at
 // the tile shape's sustained fraction of peak, plus, when tiles are cut, the
 // last arriver's reduction (one CU reads nkc partial tiles) and the partial
@@ -994,16 +998,19 @@ constexpr double kLaunch = 5e-6;
 constexpr double kParFixed = 3e-6;  // the wait for a tile's slowest workgroup and the departure
 constexpr double kCuPeak = 2.5e15 / 256.0;  // bf16 MFMA FLOP/s of one CU
 constexpr int kTileShapes[] = {kTile256x256, kTile192x256, kTile160x256, kTile128x256, kTile96x256, kTile96x128,
-                               kTile128x128};
+                               kTile128x128, kTile160x128, kTile192x128};
 // sustained fraction of a CU's MFMA peak with k-blocked x
-double tile_eff(int tile) {
+double tile_eff(int tile, int grid) {
   switch (tile) {
     case kTile256x256: return 0.64;
     case kTile192x256:
     case kTile160x256: return 0.58;
     case kTile128x256: return 0.50;
     case kTile96x256: return 0.40;
-    default: return 0.32;  // 96 x 128 and 128 x 128
+    case kTile192x128: return 0.42;
+    case kTile160x128: return 0.38;
+    case kTile128x128: return grid <= 256 ? 0.34 : 0.32;  // 8 or 4 waves
+    default: return 0.32;  // 96 x 128
   }
 }
 // workgroups of the shape a CU holds at once (LDS and registers): two of the
@@ -1015,7 +1022,7 @@ double tile_cost(const GemmPlan& p, int M, int N, int K) {
   // a CU takes a second workgroup only when the grid has more than one per CU
   const double per_cu = std::max(1.0, std::min((double)tile_occupancy(p.tile), std::ceil(wgs / 256.0)));
   const double rounds = std::ceil(wgs / (256.0 * per_cu));
-  double t = rounds * per_cu * 2.0 * bm * bn * (64.0 * p.stages_per_chunk) / (kCuPeak * tile_eff(p.tile));
+  double t = rounds * per_cu * 2.0 * bm * bn * (64.0 * p.stages_per_chunk) / (kCuPeak * tile_eff(p.tile, p.grid));
   if (p.nkc > 1) {
     // cut tiles: one CU reads the nkc partial tiles (last arriver), or, with
     // the slice reduction, each of the nkc workgroups reads one tile's worth

@@ -639,14 +639,18 @@ bool tile_one_segment(const GemmPlan& p, int K) {
 int tile_bm(int cfg) {
   switch (cfg) {
     case kTile256x256: return 256;
-    case kTile192x256: return 192;
-    case kTile160x256: return 160;
+    case kTile192x256:
+    case kTile192x128: return 192;
+    case kTile160x256:
+    case kTile160x128: return 160;
     case kTile96x256:
     case kTile96x128: return 96;
     default: return 128;
   }
 }
-int tile_bn(int cfg) { return cfg == kTile128x128 || cfg == kTile96x128 ? 128 : 256; }
+int tile_bn(int cfg) {
+  return cfg == kTile128x128 || cfg == kTile96x128 || cfg == kTile160x128 || cfg == kTile192x128 ? 128 : 256;
+}
 
 hipError_t launch_gemm_tile(const void* x, const void* w, void* y, int M, int N, int K, int epi, const GemmPlan& p,
                             int* counters, float* part, hipStream_t s, float* stats, bool x_kblocked,
@@ -694,9 +698,25 @@ hipError_t launch_gemm_tile(const void* x, const void* w, void* y, int M, int N,
     // 8 waves of 48 x 64 and of 48 x 32: more, smaller tiles where the
     // weight matrix has few rows
     case kTile96x256: return launch_shape_any<96, 256, 2, 4, 4>(a, epi, one_segment, s);
-    case kTile96x128: return launch_shape_any<96, 128, 2, 4, 4>(a, epi, one_segment, s);
+    // several M tiles on up to one workgroup per CU: twice the stages in flight
+    // instead of room for a second workgroup (8B O 305 rows 28.3 -> 26.4 us, 600
+    // rows 37.6 -> 33.2, 7B QKV 512 rows 32.5 -> 28.5; with one M tile the
+    // longer prologue costs 2%: 8B QKV 80 rows 19.9 -> 20.4)
+    case kTile96x128:
+      if (p.grid <= 256 && p.mblocks > 1) return launch_shape_any<96, 128, 2, 4, 8>(a, epi, one_segment, s);
+      return launch_shape_any<96, 128, 2, 4, 4>(a, epi, one_segment, s);
+    // 8 waves of 80 x 32 and 96 x 32: windows of 129..192 rows in one row of
+    // tiles, weights read once (8B gate/up 160 rows 64.5 -> 60.2 us, 192 rows
+    // 73.3 -> 61.7..64.3; down 160 rows 53.5 -> 42.2)
+    case kTile160x128: return launch_shape_any<160, 128, 2, 4, 8>(a, epi, one_segment, s);
+    case kTile192x128: return launch_shape_any<192, 128, 2, 4, 6>(a, epi, one_segment, s);
     case kTile128x256: return launch_shape_any<128, 256, 2, 4, 4>(a, epi, one_segment, s);
-    default: return launch_shape_any<128, 128, 2, 2, 4>(a, epi, one_segment, s);
+    // up to one workgroup per CU: 8 waves and 8 stages (8B gate/up 80 rows
+    // 50.4 -> 47.3 us, 7B down 256 rows split in 4 61.7 -> 58.8); more: two
+    // resident workgroups of 4 waves (8B gate/up 256 rows 90 against 85)
+    default:
+      if (p.grid <= 256) return launch_shape_any<128, 128, 2, 4, 8>(a, epi, one_segment, s);
+      return launch_shape_any<128, 128, 2, 2, 4>(a, epi, one_segment, s);
   }
 }
 

@@ -248,6 +248,50 @@ def test_gemm_kblocked_operands_match_row_major(kernel, split, M, N, K, epi):
                           epi | nb.NJ_GEMM_KBLOCKED, nb.NJ_GEMM_STREAM, 0, ws.data_ptr(), nbytes, _stream())
 
 
+@pytest.mark.parametrize("kernel,M,N,K,epi", [
+    (nb.NJ_GEMM_AUTO, 150, 2 * 14336, 512, nb.NJ_GEMM_SWIGLU),       # 160x128, one ragged row of tiles
+    (nb.NJ_GEMM_AUTO, 160, 28672, 512, nb.NJ_GEMM_STORE),            # 160x128, full
+    (nb.NJ_GEMM_AUTO, 150, 4096, 14336, nb.NJ_GEMM_RESIDUAL),        # 160x128, split K
+    (nb.NJ_GEMM_AUTO, 190, 2 * 14336, 512, nb.NJ_GEMM_SWIGLU),       # 192x128, ragged
+    (nb.NJ_GEMM_AUTO, 192, 28672 - 16, 512, nb.NJ_GEMM_STORE),       # 192x128, ragged columns
+    (nb.NJ_GEMM_TILE_128x128, 257, 128 * 85, 128, nb.NJ_GEMM_STORE),  # 255 workgroups: 8 waves, fewer stages than buffers
+    (nb.NJ_GEMM_TILE_128x128, 257, 128 * 86, 128, nb.NJ_GEMM_STORE),  # 258: 4 waves, two workgroups per CU
+    (nb.NJ_GEMM_TILE_96x128, 193, 128 * 85, 64, nb.NJ_GEMM_RESIDUAL),  # 255, several M tiles: 8 stage buffers
+    (nb.NJ_GEMM_TILE_96x128, 193, 128 * 86, 64, nb.NJ_GEMM_RESIDUAL),  # 258: 4
+    (nb.NJ_GEMM_TILE_96x128, 90, 128 * 40 - 48, 448, nb.NJ_GEMM_STORE),  # one M tile: 4
+])
+def test_gemm_small_tile_shapes(kernel, M, N, K, epi):
+    """The tile shapes and buffer depths of windows of up to ~600 rows, at the
+    edges of their rules, row-major and k-blocked x: the same bytes, within
+    the tolerance of the reference."""
+    x, w, y0 = _gemm_case(M, N, K, epi, seed=M + N + K + kernel)
+    Nout = N // 2 if epi == nb.NJ_GEMM_SWIGLU else N
+    dw = _devw(w)
+    nbytes = nb.gemm_plan_workspace_bytes(nb.NJ_BF16, M, N, K, epi, kernel, 0)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    nb.workspace_init(ws.data_ptr(), nbytes, _stream())
+    outs = []
+    for kb in (False, True):
+        dx = _dev(_kblock(x, M, K).reshape(M, K) if kb else x)
+        if epi == nb.NJ_GEMM_SWIGLU:
+            y = torch.empty((M, Nout), dtype=torch.int16, device="cuda")
+        elif epi == nb.NJ_GEMM_RESIDUAL:
+            y = _dev(y0.copy())
+        else:
+            y = torch.full((M, Nout), float("nan"), dtype=torch.float32, device="cuda")
+        nb.gemm_with_plan(nb.NJ_BF16, dx.data_ptr(), dw.data_ptr(), y.data_ptr(), M, N, K,
+                          epi | (nb.NJ_GEMM_KBLOCKED if kb else 0), kernel, 0, ws.data_ptr(), nbytes, _stream())
+        torch.cuda.synchronize()
+        got = y.cpu().numpy()
+        if kb and epi == nb.NJ_GEMM_SWIGLU:
+            got = got.reshape(-1).reshape(Nout // 32, M, 32).transpose(1, 0, 2).reshape(M, Nout)
+        outs.append(np.ascontiguousarray(got))
+    assert np.array_equal(outs[0].view(np.uint8), outs[1].view(np.uint8))
+    ref = _gemm_ref(x, w, epi, y0)
+    assert np.abs(_gemm_out(torch.from_numpy(outs[0]), epi) - ref).max() <= _gemm_tol(ref, epi)
+    assert nb.device_error(ws.data_ptr(), nbytes, _stream()) == 0
+
+
 @pytest.mark.parametrize("M,N,K,epi", [
     (256, 1040, 576, nb.NJ_GEMM_STORE),             # first window that copies; K of 4.5 copy blocks, ragged N
     (257, 1024, 64, nb.NJ_GEMM_RESIDUAL),           # one k step, a row past the copy's 16
