@@ -997,11 +997,12 @@ namespace {
 constexpr double kLaunch = 5e-6;
 constexpr double kParFixed = 3e-6;  // the wait for a tile's slowest workgroup and the departure
 constexpr double kCuPeak = 2.5e15 / 256.0;  // bf16 MFMA FLOP/s of one CU
-constexpr int kTileShapes[] = {kTile256x256, kTile192x256, kTile160x256, kTile128x256, kTile96x256, kTile96x128,
+constexpr int kTileShapes[] = {kTile320x256, kTile256x256, kTile192x256, kTile160x256, kTile128x256, kTile96x256, kTile96x128,
                                kTile128x128, kTile160x128, kTile192x128};
 // sustained fraction of a CU's MFMA peak with k-blocked x
-double tile_eff(int tile, int grid) {
+double tile_eff(int tile, int grid, int mblocks) {
   switch (tile) {
+    case kTile320x256: return mblocks == 1 ? 0.70 : 0.64;  // the other shapes gain more from weights shared in L2
     case kTile256x256: return 0.64;
     case kTile192x256:
     case kTile160x256: return 0.58;
@@ -1022,7 +1023,7 @@ double tile_cost(const GemmPlan& p, int M, int N, int K) {
   // a CU takes a second workgroup only when the grid has more than one per CU
   const double per_cu = std::max(1.0, std::min((double)tile_occupancy(p.tile), std::ceil(wgs / 256.0)));
   const double rounds = std::ceil(wgs / (256.0 * per_cu));
-  double t = rounds * per_cu * 2.0 * bm * bn * (64.0 * p.stages_per_chunk) / (kCuPeak * tile_eff(p.tile, p.grid));
+  double t = rounds * per_cu * 2.0 * bm * bn * (64.0 * p.stages_per_chunk) / (kCuPeak * tile_eff(p.tile, p.grid, p.mblocks));
   if (p.nkc > 1) {
     // cut tiles: one CU reads the nkc partial tiles (last arriver), or, with
     // the slice reduction, each of the nkc workgroups reads one tile's worth
@@ -1058,12 +1059,12 @@ GemmPlan gemm_tile_choose(int M, int N, int K, int epi, int only_tile) {
   for (int tile : kTileShapes) {
     if (only_tile != kTileNone && tile != only_tile) continue;
     for (int nkc = 1; nkc <= 8; nkc *= 2) {
-      if (nkc > 1 && K / 64 / nkc < 8) break;
+      if (nkc > 1 && (K / 64 / nkc < 8 || tile == kTile320x256)) break;  // that tile runs whole sums only
       consider(gemm_tile_plan(M, N, K, epi, tile, nkc));
     }
     // Stream-K on one workgroup per CU when the tiles leave CUs idle (not for
     // the 256 x 256 tile, which runs one segment per workgroup).
-    if (tile != kTile256x256 && (long)gemm_tile_plan(M, N, K, epi, tile, 1).grid % 256 != 0)
+    if (tile != kTile256x256 && tile != kTile320x256 && (long)gemm_tile_plan(M, N, K, epi, tile, 1).grid % 256 != 0)
       consider(gemm_tile_plan_sk(M, N, K, epi, tile, 256));
   }
   return best;

@@ -181,6 +181,14 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(TileK a) {
   constexpr int UPW = (XU + WU + NW - 1) / NW;
   constexpr int STAGE = (XU + WU) * 512;           // bf16 elements per stage buffer
   constexpr int DIST = NBUF - 1;                   // stages in flight ahead of the one multiplied
+  // More than 8 x fragments per wave (320-row tiles, 160 accumulators): no
+  // room for two sets of them, so they pass through a ring of XR registers,
+  // each read from LDS XD rows before its multiplies.  The stage multiplied is
+  // then still being read, and the loads of a step go to the buffer of the
+  // stage before it.
+  constexpr bool RING = TM > 8;
+  constexpr int XR = 5, XD = 4;
+  static_assert(!RING || (TM % XR == 0 && XD < XR && NBUF >= 4 && NBUF % 2 == 0), "x fragment ring");
   constexpr int HALF = BN / 2;                     // SwiGLU: gate rows, then up rows
   static_assert(NG == 1 || (TN % 2 == 0), "SwiGLU waves hold gate and up fragments in pairs");
   static_assert(DIST * UPW <= 63, "load counter range");
@@ -306,7 +314,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(TileK a) {
 
   // Fragments go through two register sets: those of stage st+1 are read
   // from LDS while stage st is multiplied.
-  bf16x8 xf[2][TM], wf[2][TN];
+  bf16x8 xf[RING ? 1 : 2][RING ? XR : TM], wf[2][TN];
 
   // a unit is two stages here (a stage is one 32-wide k-step)
   const int st0 = 2 * ku0, st1 = min(KS, 2 * ku1);
@@ -328,8 +336,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(TileK a) {
       if (q * 4 < a.nt_in) asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(ssq_v[q]) : "v"(sp + 4 * q) : "memory");
   }
 #pragma unroll
-  for (int d = 0; d < NBUF; ++d) issue(min(st0 + d, st1 - 1), d);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NBUF - 1) * UPW) : "memory");
+  for (int d = 0; d < (RING ? NBUF - 1 : NBUF); ++d) issue(min(st0 + d, st1 - 1), d);
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((RING ? NBUF - 2 : NBUF - 1) * UPW) : "memory");
   if (rinv_row) {  // 1/rms of row m0 + t (partials summed in order); read after later barriers
 #pragma unroll
     for (int q = 0; q < kMaxSsq4; ++q) asm volatile("" : "+v"(ssq_v[q]));
@@ -344,7 +352,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(TileK a) {
 #pragma unroll
   for (int j = 0; j < TN; ++j) wf[0][j] = ld16(wrd[0] + wofs(j) * 512);
 #pragma unroll
-  for (int i = 0; i < TM; ++i) xf[0][i] = ld16(xrd[0] + i * 512);
+  for (int i = 0; i < (RING ? XD : TM); ++i) xf[0][i] = ld16(xrd[0] + i * 512);
   // Step st (stage st sits in buffer (st - st0) % NBUF): stage st+1 has
   // landed in this wave's units once at most the NBUF-2 later stages' loads
   // are outstanding, and in every wave's after the barrier -- by which time
@@ -359,13 +367,35 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(TileK a) {
   auto step = [&](auto pc, auto bc, int st) {
     constexpr int P = decltype(pc)::value, Q = 1 - P;
     constexpr int BUF = decltype(bc)::value, RBUF = (BUF + 1) % NBUF;
+    if constexpr (RING) {
+      // stage st+1 has landed once at most the NBUF-3 later stages' loads are
+      // outstanding; every wave's reads of stage st-1 were consumed by its
+      // multiplies of step st-1, so its buffer takes stage st+NBUF-1
+      constexpr int LBUF = (BUF + NBUF - 1) % NBUF;
+      const int lst = min(st + NBUF - 1, st1 - 1);
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NBUF - 3) * UPW) : "memory");
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = i * UPW / TM; q < (i + 1) * UPW / TM; ++q) issue1(q, lst, LBUF);
+        xf[0][(i + XD) % XR] = i + XD < TM ? ld16(xrd[BUF] + (i + XD) * 512) : ld16(xrd[RBUF] + (i + XD - TM) * 512);
+#pragma unroll
+        for (int e = i * TN / TM; e < (i + 1) * TN / TM; ++e) wf[Q][e] = ld16(wrd[RBUF] + wofs(e) * 512);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[P][j], xf[0][i % XR], acc[i][j], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      return;
+    }
     const int nst = min(st + NBUF, st1 - 1);
     // LDS reads first, as a wait the compiler sees (so it knows every
     // fragment register has landed), then the loads and the barrier
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((NBUF - 2) * UPW) : "memory");
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
+    for (int i = 0; i < (RING ? 0 : TM); ++i) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int q = i * UPW / TM; q < (i + 1) * UPW / TM; ++q) issue1(q, nst, BUF);
@@ -638,6 +668,7 @@ bool tile_one_segment(const GemmPlan& p, int K) {
 
 int tile_bm(int cfg) {
   switch (cfg) {
+    case kTile320x256: return 320;
     case kTile256x256: return 256;
     case kTile192x256:
     case kTile192x128: return 192;
@@ -691,6 +722,15 @@ hipError_t launch_gemm_tile(const void* x, const void* w, void* y, int M, int N,
     case kTile256x256:
       if (!one_segment) return hipErrorInvalidValue;
       return launch_shape<256, 256, 2, 4, 4, false>(a, epi, s);
+    // 8 waves of 160 x 64 (x fragments through a ring, no second set): a tile
+    // multiplies 142 times per byte it loads (160 x 256: 98), and what holds
+    // these loops back is bytes through the CU's L1.  Whole sums only.  LM head
+    // of the 8B shape at 305 rows 345 -> 294 us (76% of the rate a large
+    // library product reaches), 600 rows 605 -> 535, 7B gate/up 305 rows
+    // 106 -> 98, 8B gate/up 600 rows 140 -> 120
+    case kTile320x256:
+      if (!one_segment || split) return hipErrorInvalidValue;
+      return launch_shape<320, 256, 2, 4, 4, false>(a, epi, s);
     // 8 waves of 96 x 64: windows of 3 x 128 (or 6 x 64) rows without a padded tile
     case kTile192x256: return launch_shape_any<192, 256, 2, 4, 4>(a, epi, one_segment, s);
     // 8 waves of 80 x 64: windows of 2 x 160 rows (320 = B 64 x (k+1) 5)

@@ -18,7 +18,7 @@ enum { kEpiStore = 0, kEpiResidual = 1, kEpiSwiglu = 2, kEpiLogits = 3, kEpiResi
 
 // Output tiles of the LDS-tiled kernel for large windows: x rows x weight rows.
 enum { kTileNone = 0, kTile256x256 = 1, kTile128x256 = 2, kTile128x128 = 3, kTile192x256 = 4, kTile160x256 = 5,
-       kTile96x256 = 6, kTile96x128 = 7, kTile160x128 = 8, kTile192x128 = 9 };
+       kTile96x256 = 6, kTile96x128 = 7, kTile160x128 = 8, kTile192x128 = 9, kTile320x256 = 10 };
 
 // How the bf16 GEMM splits its work.  Weight-streaming kernel (tile ==
 // kTileNone): 16-row x tiles per workgroup (mt), waves per workgroup (nw, 8),

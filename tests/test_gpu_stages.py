@@ -252,6 +252,9 @@ def test_gemm_kblocked_operands_match_row_major(kernel, split, M, N, K, epi):
     (nb.NJ_GEMM_AUTO, 150, 2 * 14336, 512, nb.NJ_GEMM_SWIGLU),       # 160x128, one ragged row of tiles
     (nb.NJ_GEMM_AUTO, 160, 28672, 512, nb.NJ_GEMM_STORE),            # 160x128, full
     (nb.NJ_GEMM_AUTO, 150, 4096, 14336, nb.NJ_GEMM_RESIDUAL),        # 160x128, split K
+    (nb.NJ_GEMM_AUTO, 310, 256 * 200 + 16, 192, nb.NJ_GEMM_STORE),   # 320x256, ragged both ways, 6 stages
+    (nb.NJ_GEMM_AUTO, 320, 2 * 128 * 220, 64, nb.NJ_GEMM_SWIGLU),    # 320x256, fewer stages than buffers
+    (nb.NJ_GEMM_AUTO, 257, 256 * 210, 320, nb.NJ_GEMM_RESIDUAL),     # 320x256, 10 stages
     (nb.NJ_GEMM_AUTO, 190, 2 * 14336, 512, nb.NJ_GEMM_SWIGLU),       # 192x128, ragged
     (nb.NJ_GEMM_AUTO, 192, 28672 - 16, 512, nb.NJ_GEMM_STORE),       # 192x128, ragged columns
     (nb.NJ_GEMM_TILE_128x128, 257, 128 * 85, 128, nb.NJ_GEMM_STORE),  # 255 workgroups: 8 waves, fewer stages than buffers
