@@ -62,6 +62,12 @@ __device__ __forceinline__ u32x2* out_at(const AttnK& a, int m, int c) {
                                          : a.out + (size_t)m * a.H * kD + c);
 }
 
+// Weight of a partial (o, max m, sum) relative to the max mx of all of them.
+// m = -inf: no finite or infinite score, so (o, sum) are zeros, or NaN where
+// every score was NaN (the max drops NaN): weighted 0 and still added, which
+// keeps the NaN.
+__device__ __forceinline__ float rel_weight(float m, float mx) { return m == -INFINITY ? 0.f : exp2f(m - mx); }
+
 // A split has written its partial (o, max, sum) with device-coherent stores;
 // count it in, and let the last split of the (sequence, KV head) to arrive
 // merge all splits in split order:
@@ -116,17 +122,14 @@ __device__ void split_arrive(const AttnK& a, int pair, int nsplit, int slot0, in
         for (int j = 0; j < kMergeSplits; ++j)
           if (s0 + j < nsplit) bm = fmaxf(bm, ml[q][j].x);
         const float mn = fmaxf(mx[q], bm);
-        if (mn == -INFINITY) continue;  // only empty splits so far
-        const float alpha = mx[q] == -INFINITY ? 0.f : exp2f(mx[q] - mn);
+        const float alpha = rel_weight(mx[q], mn);
         acc[q] *= alpha;
         wsum[q] *= alpha;
         mx[q] = mn;
-        // an empty split wrote only its -inf marker: its l and o slots hold
-        // whatever the workspace held before, so it is skipped, not weighted 0
 #pragma unroll
         for (int j = 0; j < kMergeSplits; ++j)
-          if (s0 + j < nsplit && ml[q][j].x != -INFINITY) {
-            const float f = exp2f(ml[q][j].x - mn);
+          if (s0 + j < nsplit) {
+            const float f = rel_weight(ml[q][j].x, mn);
             wsum[q] += f * ml[q][j].y;
             acc[q] += f * ov[q][j];
           }
@@ -410,12 +413,11 @@ __global__ __launch_bounds__(256, 2) void attn_reg_kernel(AttnK a) {
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     float wsum = 0.f;
 #pragma unroll
-    for (int w = 0; w < NP; ++w)
-      if (s_m[w][qr] != -INFINITY) {  // a wave without pairs holds zeros anyway
-        const float f = exp2f(s_m[w][qr] - mx);
-        wsum += f * s_l[w][qr];
-        acc += f * *reinterpret_cast<const f32x4*>(&s_o[w][qr * kRegRow + d]);
-      }
+    for (int w = 0; w < NP; ++w) {
+      const float f = rel_weight(s_m[w][qr], mx);
+      wsum += f * s_l[w][qr];
+      acc += f * *reinterpret_cast<const f32x4*>(&s_o[w][qr * kRegRow + d]);
+    }
     if (nsplit == 1) {
       const int i = qr / G, hh = qr % G;
       const float inv = 1.0f / wsum;

@@ -165,6 +165,33 @@ def test_attn_verify_paging_is_invisible():
     assert np.array_equal(got1, got2)
 
 
+@pytest.mark.parametrize("k", [0, 7, 11], ids=["r4", "r32", "r48"])  # one and two row tiles without LDS, the LDS kernel
+def test_attn_nan_and_inf_in_the_cache_reach_the_output(k):
+    """NaN or infinity in a valid token gives NaN where attention gives NaN, also
+    where a wave's or a KV split's scores are all NaN (their max is -inf, like
+    that of an empty one); in slots past the context it does not matter."""
+    shape, ctx = L8, np.array([100, 1024, 60, 700, 300, 40, 0], np.int32)
+    c, q, wk, wv = _attn_case(shape, ctx, k, seed=8)
+    kp, vp = (oracle.widen(c[n][0], shape.dtype).copy() for n in ("k_pages", "v_pages"))
+    t = c["block_table"]
+    kp[t[0, 2:4]] = np.nan            # one pair of blocks: all that some wave has
+    kp[t[1, 8:64]] = np.nan           # all but the first blocks: whole KV splits
+    kp[t[2, 1], :, 3, 7] = np.inf     # scores of +inf (NaN) or -inf (weight 0) by the sign of q
+    vp[t[3, 40], :, 5, 2] = np.nan    # one dim of one value
+    kp[t[4, 18], :, 300 % 16:, :] = np.nan
+    vp[t[4, 18], :, :, 300 % 16:] = np.inf
+    c = dict(c, k_pages=[_store(kp, shape.dtype)], v_pages=[_store(vp, shape.dtype)])
+    got, err = _attn_gpu(shape, c, q, wk, wv, ctx, k)
+    assert err == 0
+    with np.errstate(invalid="ignore"):
+        ref = _attn_oracle(shape, c, q, wk, wv, ctx, k)
+    lost = np.isnan(ref)
+    T = k + 1
+    assert lost[:2 * T].all() and lost[2 * T: 3 * T].any() and not lost[2 * T: 3 * T].all() and not lost[4 * T:].any()
+    assert np.array_equal(np.isnan(got), lost)
+    assert _rel_rows(np.where(lost, 0, got), np.where(lost, 0, ref)).max() <= 1e-2
+
+
 def test_attn_verify_flags_bad_blocks_without_faults():
     shape, ctx, k = L8, np.array([100, 40], np.int32), 2
     c, q, wk, wv = _attn_case(shape, ctx, k, seed=4)
