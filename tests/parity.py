@@ -104,13 +104,16 @@ def compare(gpu_acc, gpu_next, ref_logits, drafts, dprobs, uniforms, gpu_logits=
 def self_check(gpu_acc, gpu_next, gpu_logits, drafts, dprobs, uniforms):
     """The rule applied to the GPU's own logits, position by position.
 
-    Returns dict(checked, margin, mismatches): `checked` counts decisions
+    Returns dict(checked, margin, mismatches, chances): `checked` counts decisions
     compared (accept tests and draws), `margin` those within RATIO_MARGIN /
     CDF_MARGIN on these logits (a fp32 vs fp64 evaluation may take them either
-    way; the rest of that sequence is then skipped)."""
+    way; the rest of that sequence is then skipped), `chances` is for every
+    draw reached the chance of a uniform within CDF_MARGIN of a boundary of the
+    entry it draws: an entry of weight w spans w / S of the uniforms, the
+    margins cover 2 CDF_MARGIN of its w."""
     B = len(gpu_acc)
     k = drafts.shape[1] if drafts.ndim == 2 else 0
-    out = {"checked": 0, "margin": 0, "mismatches": []}
+    out = {"checked": 0, "margin": 0, "mismatches": [], "chances": []}
     for b in range(B):
         p = oracle.softmax(np.asarray(gpu_logits[b], dtype=np.float64))
         q = np.asarray(dprobs[b], dtype=np.float64) if k else np.zeros((0, p.shape[1]))
@@ -139,6 +142,7 @@ def self_check(gpu_acc, gpu_next, gpu_logits, drafts, dprobs, uniforms):
             continue
         w = _draw_weights(p, q, n, k)
         c = np.cumsum(w)
+        out["chances"].append(float(np.minimum(w, 2 * CDF_MARGIN).sum() / c[-1]))
         target = u[k] * c[-1]
         j = oracle.invcdf(w, u[k])
         lo = c[j - 1] if j > 0 else 0.0
@@ -149,6 +153,19 @@ def self_check(gpu_acc, gpu_next, gpu_logits, drafts, dprobs, uniforms):
         if int(gpu_next[b, n]) != j:
             out["mismatches"].append((b, n, "draw(self)", j, int(gpu_next[b, n])))
     return out
+
+
+def margin_limit(chances, tail=1e-3):
+    """The count of draws within the margin that independent draws of these
+    chances exceed with probability under `tail`.  Which draws fall there is
+    chance: any change of rounding in the logits moves the running sums by far
+    more than the margin.  At V = 128256 with logits of unit spread the chance
+    is 0.215 a draw, so that more than two of eight do with probability 0.24."""
+    dist = np.array([1.0])
+    for c in chances:
+        dist = np.convolve(dist, [1.0 - c, c])
+    over = 1.0 - np.cumsum(dist)
+    return int(np.argmax(over < tail))
 
 
 REPORT = []

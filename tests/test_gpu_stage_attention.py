@@ -308,3 +308,30 @@ def test_attn_splits_longer_than_the_page_ids_read_at_once(shape, B, ctx, k):
         got = wide(out[b * T: (b + 1) * T]).view(T, Hkv, G, D)
         # bf16 probabilities and output: 2^-9 relative roundings
         assert float((got - ref).norm() / ref.norm()) < 5e-3
+
+
+@pytest.mark.parametrize("k", [3, 7, 11], ids=["r16", "r32", "r48"])  # both kernels, one and two row tiles
+def test_attn_leading_token_is_not_rounded(k):
+    """A late token leads every row by about 5 (log2) and alone has a value: its
+    probability relative to the row's max is 1, exact in bf16, so the output is
+    v * p / sum with one rounding, of the output itself: half a bf16 spacing,
+    2^-8 of the power of two below it (fp32 terms under 2^-14)."""
+    shape, ctx = L8, np.array([300, 77, 650], np.int32)
+    c, q, wk, wv = _attn_case(shape, ctx, k, seed=6)
+    rng = np.random.default_rng(7)
+    Hkv, D = shape.n_kv_heads, shape.head_dim
+    u = np.where(rng.standard_normal(D) < 0, -1.0, 1.0)
+    q = _store(np.broadcast_to(u, q.shape), shape.dtype)
+    kp, vp = np.zeros(c["k_pages"][0].shape, np.float32), np.zeros(c["v_pages"][0].shape, np.float32)
+    for b, n in enumerate(ctx):
+        blk, pos = c["block_table"][b, (n - 2) // 16], (n - 2) % 16
+        kp[blk, :, pos, :] = u * rng.uniform(0.28, 0.38, size=(Hkv, 1))  # scores 3.2 to 4.3 above the others' 0
+        vp[blk, :, :, pos] = rng.standard_normal((Hkv, D))
+    c = dict(c, k_pages=[_store(kp, shape.dtype)], v_pages=[_store(vp, shape.dtype)])
+    wk, wv = np.zeros_like(wk), np.zeros_like(wv)
+    got, err = _attn_gpu(shape, c, q, wk, wv, ctx, k)
+    assert err == 0
+    ref = _attn_oracle(shape, c, q, wk, wv, ctx, k)
+    half = np.exp2(np.floor(np.log2(np.maximum(np.abs(ref), 1e-30))) - 8)
+    off = np.abs(got - ref) - np.abs(ref) * 2.0 ** -14
+    assert (off <= half).all(), (off / half).max()

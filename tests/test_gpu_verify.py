@@ -18,7 +18,7 @@ from paper_2512_22420_amd.device import (DeviceCache, DeviceModel, StepIO, Works
                                         model_desc, verify)
 
 import rounding_model as RM
-from parity import compare, record, rel_l2_rows, self_check
+from parity import compare, margin_limit, record, rel_l2_rows, self_check
 
 pytestmark = pytest.mark.gpu
 
@@ -63,7 +63,8 @@ def _decisions_ok(io, ref, x, gpu_logits=None, min_checked=0):
         sres = self_check(acc, nxt, gpu_logits, x["draft_tokens"], x["draft_probs"], x["uniforms"])
         assert not sres["mismatches"], sres["mismatches"][:5]
         B = len(acc)
-        assert sres["margin"] <= max(1, B // 4), sres
+        # a quarter, or what chance explains where draws often fall in the margin (large vocabularies)
+        assert sres["margin"] <= max(1, B // 4, margin_limit(sres["chances"])), sres
         assert sres["checked"] >= B - sres["margin"], sres
     record(res, sres)
     assert not res["mismatches"], res["mismatches"][:5]
