@@ -432,7 +432,8 @@ enum {
  * M >= 1; for bf16 K % 32 == 0 and the output width % 16 == 0.  workspace:
  * device, 256-byte aligned, at least nightjar_gemm_workspace_bytes(...) bytes,
  * prepared once with nightjar_workspace_init (split-K counters start at zero
- * and are left at zero by every call).  A call may write partial sums and a
+ * and are left at zero by every call); one workspace may serve calls of
+ * different shapes in turn, if it has the bytes of each.  A call may write partial sums and a
  * k-blocked copy of x into it: calls that overlap in time need workspaces of
  * their own.
  */

@@ -910,11 +910,13 @@ static size_t gemm_xcopy_bytes(const GemmPlan& p, int32_t M, int32_t N, int32_t 
   const bool pays = M >= 256 || N >= 16384;
   return p.tile != kTileNone && pays && M <= kKblockMaxRows && bytes <= ((size_t)256 << 20) ? al(bytes) : 0;
 }
-// Where the copy starts: past the split's counters and partials, and past the
-// counters of any other shape that shares the workspace (zero between calls).
-static size_t gemm_xcopy_offset(const GemmPlan& p) {
-  return kAlign + std::max(p.counter_bytes + p.part_bytes, kGemmCounterBytes);
-}
+// A GEMM workspace: [device error word][counters][partials][k-blocked x].  A
+// split plan's partials lie past the counters that any plan may have, not only
+// its own, so that calls of other shapes on the same workspace find their
+// counters as they left them (zero).
+static size_t gemm_part_offset(const GemmPlan& p) { return p.part_bytes ? kAlign + kGemmCounterBytes : kAlign; }
+static size_t gemm_plan_bytes(const GemmPlan& p) { return gemm_part_offset(p) + p.part_bytes; }
+static size_t gemm_xcopy_offset(const GemmPlan& p) { return kAlign + kGemmCounterBytes + p.part_bytes; }
 
 size_t nightjar_gemm_workspace_bytes(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t epilogue) {
   epilogue &= ~NJ_GEMM_KBLOCKED;
@@ -922,7 +924,7 @@ size_t nightjar_gemm_workspace_bytes(int32_t dtype, int32_t M, int32_t N, int32_
   if (dtype != NJ_BF16) return kAlign;
   const GemmPlan p = gemm_plan(M, N, K, epilogue);
   const size_t xcopy = gemm_xcopy_bytes(p, M, N, K);
-  return xcopy ? gemm_xcopy_offset(p) + xcopy : kAlign + p.counter_bytes + p.part_bytes;
+  return xcopy ? gemm_xcopy_offset(p) + xcopy : gemm_plan_bytes(p);
 }
 
 int nightjar_gemm(int32_t dtype, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,
@@ -937,10 +939,10 @@ int nightjar_gemm(int32_t dtype, const void* x, const void* w, void* y, int32_t 
   if (dtype == NJ_BF16 && (!aligned16(x) || !aligned16(w) || !aligned16(y)))
     return fail(NJ_EINVAL, "operands must be 16-byte aligned");
   const GemmPlan p = dtype == NJ_BF16 ? gemm_plan(M, N, K, epilogue) : GemmPlan{};
-  const size_t need = kAlign + p.counter_bytes + p.part_bytes;
+  const size_t need = gemm_plan_bytes(p);
   if (!workspace || workspace_bytes < need) return fail(NJ_EINVAL, "workspace NULL or smaller than %zu bytes", need);
   if (((uintptr_t)workspace & (kAlign - 1)) != 0) return fail(NJ_EINVAL, "workspace must be 256-byte aligned");
-  char* ws = static_cast<char*>(workspace) + kAlign;  // [counters][partials], then the k-blocked x
+  char* ws = static_cast<char*>(workspace);
   hipStream_t s = (hipStream_t)stream;
   hipError_t e;
   if (dtype != NJ_BF16) {
@@ -949,13 +951,13 @@ int nightjar_gemm(int32_t dtype, const void* x, const void* w, void* y, int32_t 
     const size_t xcopy = kb ? 0 : gemm_xcopy_bytes(p, M, N, K);
     const bool copy = xcopy > 0 && workspace_bytes >= gemm_xcopy_offset(p) + xcopy;
     if (copy) {
-      char* xk = static_cast<char*>(workspace) + gemm_xcopy_offset(p);
+      char* xk = ws + gemm_xcopy_offset(p);
       e = launch_kblock(x, xk, M, K, s);
       if (e != hipSuccess) return hip_fail(e, "gemm: k-blocked x");
       x = xk;
     }
-    e = launch_gemm_plan(x, w, y, M, N, K, epilogue, p, reinterpret_cast<int*>(ws),
-                         reinterpret_cast<float*>(ws + p.counter_bytes), s, kb || copy, kb && epilogue == NJ_GEMM_SWIGLU);
+    e = launch_gemm_plan(x, w, y, M, N, K, epilogue, p, reinterpret_cast<int*>(ws + kAlign),
+                         reinterpret_cast<float*>(ws + gemm_part_offset(p)), s, kb || copy, kb && epilogue == NJ_GEMM_SWIGLU);
   }
   return e == hipSuccess ? NJ_OK : hip_fail(e, "gemm");
 }
@@ -1007,7 +1009,7 @@ size_t nightjar_gemm_plan_workspace_bytes(int32_t dtype, int32_t M, int32_t N, i
   epilogue &= ~NJ_GEMM_KBLOCKED;
   GemmPlan p;
   if (plan_with(dtype, M, N, K, epilogue, kernel, split_k, &p) != NJ_OK) return 0;
-  return dtype == NJ_BF16 ? kAlign + p.counter_bytes + p.part_bytes : kAlign;
+  return dtype == NJ_BF16 ? gemm_plan_bytes(p) : kAlign;
 }
 
 int nightjar_gemm_with_plan(int32_t dtype, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,
@@ -1022,14 +1024,14 @@ int nightjar_gemm_with_plan(int32_t dtype, const void* x, const void* w, void* y
   if (!x || !w || !y) return fail(NJ_EINVAL, "NULL operand");
   if (dtype == NJ_BF16 && (!aligned16(x) || !aligned16(w) || !aligned16(y)))
     return fail(NJ_EINVAL, "operands must be 16-byte aligned");
-  const size_t need = dtype == NJ_BF16 ? kAlign + p.counter_bytes + p.part_bytes : kAlign;
+  const size_t need = dtype == NJ_BF16 ? gemm_plan_bytes(p) : kAlign;
   if (!workspace || workspace_bytes < need) return fail(NJ_EINVAL, "workspace NULL or smaller than %zu bytes", need);
   if (((uintptr_t)workspace & (kAlign - 1)) != 0) return fail(NJ_EINVAL, "workspace must be 256-byte aligned");
-  char* ws = static_cast<char*>(workspace) + kAlign;  // [counters][partials]
+  char* ws = static_cast<char*>(workspace);
   hipError_t e;
   if (dtype == NJ_BF16)
-    e = launch_gemm_plan(x, w, y, M, N, K, epilogue, p, reinterpret_cast<int*>(ws),
-                         reinterpret_cast<float*>(ws + p.counter_bytes), (hipStream_t)stream, kb,
+    e = launch_gemm_plan(x, w, y, M, N, K, epilogue, p, reinterpret_cast<int*>(ws + kAlign),
+                         reinterpret_cast<float*>(ws + gemm_part_offset(p)), (hipStream_t)stream, kb,
                          kb && epilogue == NJ_GEMM_SWIGLU);
   else
     e = launch_gemm(kF32, x, w, y, M, N, K, epilogue, nullptr, nullptr, (hipStream_t)stream);

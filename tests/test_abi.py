@@ -127,6 +127,21 @@ def test_gemm_with_plan_rejects_impossible_plans_on_host():
                                      b - 1, 0) == nb.NJ_EINVAL
 
 
+def test_gemm_partials_lie_past_the_counters_of_every_shape():
+    """Calls of different shapes may share a workspace: a split plan's partial
+    sums start past the region in which any plan keeps its counters (1024 of
+    256 bytes, behind the 256-byte error word), not right behind its own."""
+    counters, res = 256 + 1024 * 256, nb.NJ_GEMM_RESIDUAL
+    for kernel, split, M, N, K in [(nb.NJ_GEMM_STREAM, 2, 16, 128, 4096), (nb.NJ_GEMM_STREAM, 8, 39, 4096, 14336),
+                                   (nb.NJ_GEMM_TILE_128x128, 4, 160, 4096, 14336), (nb.NJ_GEMM_TILE_96x128, 2, 96, 128, 512)]:
+        need = nb.gemm_plan_workspace_bytes(nb.NJ_BF16, M, N, K, res, kernel, split)
+        assert need >= counters + split * M * N * 4, (kernel, split, M, N, K, need)
+    # the planner's own choice for the 8B down projection at 39 rows splits K
+    need = nb.gemm_workspace_bytes(nb.NJ_BF16, 39, 4096, 14336, res)
+    assert need >= counters + 2 * 39 * 4096 * 4
+    assert nb.gemm_plan_workspace_bytes(nb.NJ_BF16, 39, 4096, 14336, res, nb.NJ_GEMM_AUTO, 0) == need
+
+
 def test_stage_entries_reject_bad_arguments_on_host():
     desc = model_desc(W.QWEN7B)  # G = 7: k = 9 gives 70 query rows per KV head
     n = nb.attn_workspace_bytes(desc, 1, 9)

@@ -525,6 +525,29 @@ def test_gemm_split_k_is_deterministic_and_reusable():
     assert not torch.isnan(outs[0]).any()
 
 
+def test_gemm_shapes_share_one_workspace():
+    """Split plans with few and with many counters, and one of the tiled kernel,
+    in turn on one workspace: each result is that of a workspace of its own and
+    the counters are zero after every call."""
+    K, epi = 14336, nb.NJ_GEMM_RESIDUAL
+    shapes = [(39, 4096), (160, 4096), (39, 4096), (300, 2048), (160, 4096)]
+    assert all(nb.gemm_workspace_bytes(nb.NJ_BF16, M, N, K, epi) >= 2 * M * N * 4 for M, N in shapes)  # they all split
+    shared = max(nb.gemm_workspace_bytes(nb.NJ_BF16, M, N, K, epi) for M, N in shapes)
+    ws = torch.empty(shared, dtype=torch.uint8, device="cuda")
+    nb.workspace_init(ws.data_ptr(), shared, _stream())
+    for M, N in shapes:
+        x, w, y0 = _gemm_case(M, N, K, epi, seed=M + N)
+        dx, dw = _dev(x), _devw(w)
+        y = _dev(y0.copy())
+        nb.gemm(nb.NJ_BF16, dx.data_ptr(), dw.data_ptr(), y.data_ptr(), M, N, K, epi, ws.data_ptr(), shared, _stream())
+        own = _dev(y0.copy())
+        _gemm(nb.NJ_BF16, dx, dw, own, M, N, K, epi)
+        assert torch.equal(y, own), (M, N)
+        assert not ws[: 256 + 1024 * 256].any(), (M, N)
+        ref = _gemm_ref(x, w, epi, y0)
+        assert np.abs(_gemm_out(y, epi) - ref).max() <= _gemm_tol(ref, epi)
+
+
 @pytest.mark.parametrize("N,K", [(16, 32), (300, 96), (128, 4096), (2 * 688, 256)])
 def test_pack_weight_layout(N, K):
     """nightjar_pack_weight against the layout formula of the header, bit for
