@@ -433,9 +433,10 @@ enum {
  * device, 256-byte aligned, at least nightjar_gemm_workspace_bytes(...) bytes,
  * prepared once with nightjar_workspace_init (split-K counters start at zero
  * and are left at zero by every call); one workspace may serve calls of
- * different shapes in turn, if it has the bytes of each.  A call may write partial sums and a
- * k-blocked copy of x into it: calls that overlap in time need workspaces of
- * their own.
+ * different shapes in turn, if it has the bytes of each.  A call that asks for
+ * more than 256 bytes writes counters and partial sums into it, so such calls
+ * need workspaces of their own where they overlap in time; one that asks for
+ * 256 writes nothing there but device errors.
  */
 size_t nightjar_gemm_workspace_bytes(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t epilogue);
 int nightjar_gemm(int32_t dtype, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,

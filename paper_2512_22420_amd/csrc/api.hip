@@ -894,37 +894,18 @@ int nightjar_pack_weight(const void* src, void* dst, int32_t N, int32_t K, void*
   return e == hipSuccess ? NJ_OK : hip_fail(e, "pack_weight");
 }
 
-// A row-major x of a tiled plan is copied k-blocked into the workspace first:
-// the tile loads then read 1 KB runs instead of 16 rows of 64 bytes, each in a
-// page of its own (address translation, not bandwidth, held them up). The copy
-// is a launch of ~3-4 us and pays where x is read by many column tiles or has
-// many rows. Measured (us, direct loads -> with the copy): 7B gate/up 2048 rows
-// 499 -> 436, 600 rows 187 -> 164; 8B LM head 300 rows 403 -> 351; 8B gate/up
-// 70 rows 55 -> 51, 300 rows 94.5 -> 84; 8B down 300 rows 64.5 -> 61.5, O 300
-// rows 29 -> 26.7. Few columns and few rows lose: O 150 rows 19.5 -> 21.0, down
-// 100 rows 42.6 -> 43.8, so those read x as it is.
-// Copies of more than 256 MB are not made, nor where the caller's workspace has
-// no room for one (the direct loads remain, with the same products).
-static size_t gemm_xcopy_bytes(const GemmPlan& p, int32_t M, int32_t N, int32_t K) {
-  const size_t bytes = (size_t)M * K * 2;
-  const bool pays = M >= 256 || N >= 16384;
-  return p.tile != kTileNone && pays && M <= kKblockMaxRows && bytes <= ((size_t)256 << 20) ? al(bytes) : 0;
-}
-// A GEMM workspace: [device error word][counters][partials][k-blocked x].  A
-// split plan's partials lie past the counters that any plan may have, not only
+// A GEMM workspace: [device error word][counters][partials]; a plan that does
+// not split K uses none of it but the error word.  A split plan's partials lie past the counters that any plan may have, not only
 // its own, so that calls of other shapes on the same workspace find their
 // counters as they left them (zero).
 static size_t gemm_part_offset(const GemmPlan& p) { return p.part_bytes ? kAlign + kGemmCounterBytes : kAlign; }
 static size_t gemm_plan_bytes(const GemmPlan& p) { return gemm_part_offset(p) + p.part_bytes; }
-static size_t gemm_xcopy_offset(const GemmPlan& p) { return kAlign + kGemmCounterBytes + p.part_bytes; }
 
 size_t nightjar_gemm_workspace_bytes(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t epilogue) {
   epilogue &= ~NJ_GEMM_KBLOCKED;
   if (gemm_args_ok(dtype, M, N, K, epilogue) != NJ_OK) return 0;
   if (dtype != NJ_BF16) return kAlign;
-  const GemmPlan p = gemm_plan(M, N, K, epilogue);
-  const size_t xcopy = gemm_xcopy_bytes(p, M, N, K);
-  return xcopy ? gemm_xcopy_offset(p) + xcopy : gemm_plan_bytes(p);
+  return gemm_plan_bytes(gemm_plan(M, N, K, epilogue));
 }
 
 int nightjar_gemm(int32_t dtype, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,
@@ -943,22 +924,13 @@ int nightjar_gemm(int32_t dtype, const void* x, const void* w, void* y, int32_t 
   if (!workspace || workspace_bytes < need) return fail(NJ_EINVAL, "workspace NULL or smaller than %zu bytes", need);
   if (((uintptr_t)workspace & (kAlign - 1)) != 0) return fail(NJ_EINVAL, "workspace must be 256-byte aligned");
   char* ws = static_cast<char*>(workspace);
-  hipStream_t s = (hipStream_t)stream;
   hipError_t e;
-  if (dtype != NJ_BF16) {
-    e = launch_gemm(kF32, x, w, y, M, N, K, epilogue, nullptr, nullptr, s);
-  } else {
-    const size_t xcopy = kb ? 0 : gemm_xcopy_bytes(p, M, N, K);
-    const bool copy = xcopy > 0 && workspace_bytes >= gemm_xcopy_offset(p) + xcopy;
-    if (copy) {
-      char* xk = ws + gemm_xcopy_offset(p);
-      e = launch_kblock(x, xk, M, K, s);
-      if (e != hipSuccess) return hip_fail(e, "gemm: k-blocked x");
-      x = xk;
-    }
+  if (dtype == NJ_BF16)
     e = launch_gemm_plan(x, w, y, M, N, K, epilogue, p, reinterpret_cast<int*>(ws + kAlign),
-                         reinterpret_cast<float*>(ws + gemm_part_offset(p)), s, kb || copy, kb && epilogue == NJ_GEMM_SWIGLU);
-  }
+                         reinterpret_cast<float*>(ws + gemm_part_offset(p)), (hipStream_t)stream, kb,
+                         kb && epilogue == NJ_GEMM_SWIGLU);
+  else
+    e = launch_gemm(kF32, x, w, y, M, N, K, epilogue, nullptr, nullptr, (hipStream_t)stream);
   return e == hipSuccess ? NJ_OK : hip_fail(e, "gemm");
 }
 

@@ -12,10 +12,11 @@
 // - Operands go from memory straight into LDS (global_load_lds_dwordx4: no
 //   staging registers, no LDS write instructions), one 32-wide k-step per
 //   stage, NBUF stage buffers, NBUF-1 stages in flight.  Each stage holds
-//   1 KB units of 16 rows x 32 k in MFMA operand order (lane l: row l % 16,
-//   k 8 (l / 16) .. +8): a unit is one load instruction (lane l's 16 bytes land
-//   at byte 16 l) and one conflict-free fragment read.  Weight units are the
-//   packed layout's tiles copied as they are; x units gather 16 row segments.
+//   1 KB units of 16 rows x 32 k: a unit is one load instruction (lane l's 16
+//   bytes land at byte 16 l) and one conflict-free fragment read (lane l: row
+//   l % 16, k 8 (l / 16) .. +8).  Weight units are the packed layout's tiles,
+//   in operand order, copied as they are; x units are 16 row segments of 64
+//   bytes, swizzled (x_swizzle).
 // - Tile order is XCD-aware: workgroup IDs go round-robin over the 8 XCDs, so
 //   the linear ID is remapped to give each XCD a contiguous run of tiles, with
 //   the M tiles of one weight tile adjacent.  The weight tile is then fetched
@@ -40,6 +41,20 @@ namespace {
 __device__ __forceinline__ float silu_mul(float gte, float up) { return gte / (1.0f + expf(-gte)) * up; }
 // exp(x) = 2^(x log2 e): the statistics sum one hardware exp2 per logit
 constexpr float kLog2e = 1.4426950408889634f;
+
+// An x unit in LDS: its 16 rows of 64 bytes, the four 16-byte pieces of row r
+// (k 8 j .. 8 j + 7) at positions j ^ x_swizzle(r), so that the 16 rows' pieces
+// j, as a fragment read takes them, lie in different banks (any 8 consecutive
+// rows too).  Four consecutive lanes load one row's 64 bytes, and the L1 looks
+// its line up once for them.  In operand order (lanes 0..15 the 16 rows) a
+// row-major unit took 64 lookups and a k-blocked one 32 where 16 do, and the
+// kernel waited for the L1's lookups: 8B gate/up at 160 rows, row-major x, 24.0
+// -> 9.3 million lookups and 57.3 -> 44.8 us with the weights in the last-level
+// cache, 73.4 -> 66.7 from HBM (k-blocked 13.9 -> 9.1 million, 42.9 -> 41.9);
+// 7B at 2048 rows 186 -> 80 million, 497 -> 445 us (110 -> 75, 435 -> 425).
+// Row-major x stays behind k-blocked x: a stage takes half of each row's
+// 128-byte line, and the other half is asked for while the first is on its way.
+__device__ __forceinline__ int x_swizzle(int r) { return (((r >> 1) ^ (r >> 3)) & 1) | ((r >> 1) & 2); }
 
 struct TileK {
   const bf16_t* X;
@@ -265,10 +280,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(TileK a) {
     const int u = min(q * NW + wv, XU + WU - 1);
     if (u < XU) {
       // row-major x: 64 bytes of each of 16 rows; k-blocked x: one 1 KB run
-      const uint32_t row = (uint32_t)min(m0 + u * 16 + r, M - 1);
+      const uint32_t row = (uint32_t)min(m0 + u * 16 + (lane >> 2), M - 1);
+      const uint32_t kk = (uint32_t)((lane & 3) ^ x_swizzle(lane >> 2)) * 8;
       ubase[q] = reinterpret_cast<const char*>(a.X);
       ustep[q] = a.xkb ? (uint32_t)M * 64u : 64u;
-      vofs[q] = a.xkb ? (row * 32u + g * 8) * 2u : (row * (uint32_t)K + g * 8) * 2u;
+      vofs[q] = a.xkb ? (row * 32u + kk) * 2u : (row * (uint32_t)K + kk) * 2u;
     } else {
       const int t16 = u - XU;
       int T;
@@ -319,7 +335,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(TileK a) {
 #pragma unroll
   for (int b = 0; b < NBUF; ++b) {
     wrd[b] = lds + b * STAGE + wub * 512 + lane * 8;
-    xrd[b] = lds + b * STAGE + xub * 512 + lane * 8;
+    xrd[b] = lds + b * STAGE + xub * 512 + (r * 4 + (g ^ x_swizzle(r))) * 8;
   }
   auto ld16 = [](const bf16_t* p) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(p)); };
 
@@ -655,22 +671,7 @@ hipError_t launch_shape_any(const TileK& a, int epi, bool one_segment, hipStream
                      : launch_shape<BM, BN, WM, WN, NBUF, true>(a, epi, s);
 }
 
-// x row-major [M][K] to k-blocked [K/32][M][32], K % 64 == 0: a wave copies 4
-// rows x 128 k as 16-byte pieces (256 contiguous bytes of a row read, 256 of a
-// k block written).
-__global__ __launch_bounds__(256) void kblock_kernel(const u32x4* __restrict__ x, u32x4* __restrict__ dst, int M, int K) {
-  const int lane = threadIdx.x & 63, P = K / 8;  // 16-byte pieces per row
-  const int p = blockIdx.x * 16 + (lane & 15), row = (blockIdx.y * 4 + (threadIdx.x >> 6)) * 4 + (lane >> 4);
-  if (p < P && row < M) dst[((size_t)(p >> 2) * M + row) * 4 + (p & 3)] = x[(size_t)row * P + p];
-}
 }  // namespace
-
-hipError_t launch_kblock(const void* x, void* dst, int M, int K, hipStream_t s) {
-  if (K % 64 || M > kKblockMaxRows) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kblock_kernel, dim3((K / 8 + 15) / 16, (M + 15) / 16), dim3(256), 0, s, static_cast<const u32x4*>(x),
-                     static_cast<u32x4*>(dst), M, K);
-  return hipGetLastError();
-}
 
 bool tile_one_segment(const GemmPlan& p, int K) {
   const long tiles = (long)p.ntiles * p.mblocks;

@@ -197,10 +197,6 @@ hipError_t launch_gemm_tile(const void* x, const void* w, void* y, int M, int N,
                             float* stats = nullptr, bool x_kblocked = false, bool y_kblocked = false,
                             const GemmNorm* nm = nullptr);
 
-// A k-blocked copy of x (as launch_gemm_tile reads it) of a row-major bf16 one; K % 64 == 0.
-constexpr int kKblockMaxRows = 16 * 65535;  // its grid
-hipError_t launch_kblock(const void* x, void* dst, int M, int K, hipStream_t s);
-
 // h[r] = E[id(r)], x[r] = rmsnorm(h[r]) * gain, ids from last/draft tokens.
 struct AttnPlan;
 // The embedding kernels can carry one more workgroup that builds the

@@ -142,6 +142,15 @@ def test_gemm_partials_lie_past_the_counters_of_every_shape():
     assert nb.gemm_plan_workspace_bytes(nb.NJ_BF16, 39, 4096, 14336, res, nb.NJ_GEMM_AUTO, 0) == need
 
 
+@pytest.mark.parametrize("M,N,K,epi", [
+    (160, 28672, 4096, nb.NJ_GEMM_SWIGLU), (2048, 37888, 3584, nb.NJ_GEMM_SWIGLU), (305, 128256, 4096, nb.NJ_GEMM_STORE),
+    (256, 28672, 512, nb.NJ_GEMM_STORE), (8, 4096, 4096, nb.NJ_GEMM_RESIDUAL)])
+def test_gemm_without_split_needs_no_scratch(M, N, K, epi):
+    """A plan that does not split K keeps nothing in the workspace, so such calls
+    may overlap on one: all that is asked for is the 256 bytes of the error word."""
+    assert nb.gemm_workspace_bytes(nb.NJ_BF16, M, N, K, epi) == 256
+
+
 def test_stage_entries_reject_bad_arguments_on_host():
     desc = model_desc(W.QWEN7B)  # G = 7: k = 9 gives 70 query rows per KV head
     n = nb.attn_workspace_bytes(desc, 1, 9)

@@ -296,39 +296,64 @@ def test_gemm_small_tile_shapes(kernel, M, N, K, epi):
 
 
 @pytest.mark.parametrize("M,N,K,epi", [
-    (256, 1040, 576, nb.NJ_GEMM_STORE),             # first window that copies; K of 4.5 copy blocks, ragged N
-    (257, 1024, 64, nb.NJ_GEMM_RESIDUAL),           # one k step, a row past the copy's 16
-    (301, 512, 2048, nb.NJ_GEMM_STORE),             # split K: the copy lies past counters and partials
+    (256, 1040, 576, nb.NJ_GEMM_STORE),             # ragged N
+    (257, 1024, 64, nb.NJ_GEMM_RESIDUAL),           # one k step, a row past a unit's 16
+    (301, 512, 2048, nb.NJ_GEMM_STORE),             # split K
     (97, 2 * 8192, 192, nb.NJ_GEMM_SWIGLU),         # few rows, wide matrix
-    (255, 1024, 512, nb.NJ_GEMM_STORE),             # below the rule: no copy
+    (255, 1024, 512, nb.NJ_GEMM_STORE),
 ])
-def test_gemm_row_major_x_copied_k_blocked(M, N, K, epi):
-    """nightjar_gemm copies a row-major x k-blocked where that pays: the same
-    bytes as without the copy (a workspace with no room for it) and within the
-    tolerance of the reference, and the split counters stay zero."""
+def test_gemm_row_major_x_of_tiled_plans(M, N, K, epi):
+    """nightjar_gemm with row-major x gives the bytes that k-blocked x gives, and
+    writes only the part of a workspace that it asks for: nothing but the error
+    word where K is not split."""
     x, w, y0 = _gemm_case(M, N, K, epi, seed=M + N + K)
     Nout = N // 2 if epi == nb.NJ_GEMM_SWIGLU else N
-    dx, dw = _dev(x), _devw(w)
-    full = nb.gemm_workspace_bytes(nb.NJ_BF16, M, N, K, epi)
-    least = nb.gemm_plan_workspace_bytes(nb.NJ_BF16, M, N, K, epi, nb.NJ_GEMM_AUTO, 0)
-    assert (full > least) == (M >= 256 or N >= 16384)
-    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
-    nb.workspace_init(ws.data_ptr(), full, _stream())
+    dw = _devw(w)
+    need = nb.gemm_workspace_bytes(nb.NJ_BF16, M, N, K, epi)
+    ws = torch.full((need + M * K * 2,), 0x5a, dtype=torch.uint8, device="cuda")
+    nb.workspace_init(ws.data_ptr(), need, _stream())
     outs = []
-    for nbytes in (full, least, full):
+    for kb in (False, True):
+        dx = _dev(_kblock(x, M, K).reshape(M, K) if kb else x)
         if epi == nb.NJ_GEMM_SWIGLU:
             y = torch.empty((M, Nout), dtype=torch.int16, device="cuda")
         elif epi == nb.NJ_GEMM_RESIDUAL:
             y = _dev(y0.copy())
         else:
             y = torch.full((M, Nout), float("nan"), dtype=torch.float32, device="cuda")
-        nb.gemm(nb.NJ_BF16, dx.data_ptr(), dw.data_ptr(), y.data_ptr(), M, N, K, epi, ws.data_ptr(), nbytes, _stream())
+        nb.gemm(nb.NJ_BF16, dx.data_ptr(), dw.data_ptr(), y.data_ptr(), M, N, K, epi | (nb.NJ_GEMM_KBLOCKED if kb else 0),
+                ws.data_ptr(), ws.numel(), _stream())
         torch.cuda.synchronize()
-        outs.append(y)
-    for o in outs[1:]:
-        assert torch.equal(outs[0].view(torch.uint8), o.view(torch.uint8))
+        got = y.cpu().numpy()
+        if kb and epi == nb.NJ_GEMM_SWIGLU:
+            got = got.reshape(-1).reshape(Nout // 32, M, 32).transpose(1, 0, 2).reshape(M, Nout)
+        outs.append(np.ascontiguousarray(got))
+    assert np.array_equal(outs[0].view(np.uint8), outs[1].view(np.uint8))
     ref = _gemm_ref(x, w, epi, y0)
-    assert np.abs(_gemm_out(outs[0], epi) - ref).max() <= _gemm_tol(ref, epi)
+    assert np.abs(_gemm_out(torch.from_numpy(outs[0]), epi) - ref).max() <= _gemm_tol(ref, epi)
+    assert not ws[:256].any() and bool((ws[need:] == 0x5a).all())
+
+
+def test_gemm_unsplit_calls_overlap_on_one_workspace():
+    """Two streams, different x, one workspace of 256 bytes."""
+    M, N, K, epi = 300, 28672, 512, nb.NJ_GEMM_STORE
+    assert nb.gemm_workspace_bytes(nb.NJ_BF16, M, N, K, epi) == 256
+    ws = torch.zeros(256 + 4 * M * K, dtype=torch.uint8, device="cuda")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    w = W.device_normal_bf16(gen, (N, K), 0.03)
+    pw = pack_weight(w)
+    xs = [W.device_normal_bf16(gen, (M, K), 1.0) for _ in range(2)]
+    ys = [torch.empty((M, N), dtype=torch.float32, device="cuda") for _ in range(2)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for x, y, st in zip(xs, ys, streams):
+            nb.gemm(nb.NJ_BF16, x.data_ptr(), pw.data_ptr(), y.data_ptr(), M, N, K, epi, ws.data_ptr(), ws.numel(), st.cuda_stream)
+    torch.cuda.synchronize()
+    for x, y in zip(xs, ys):
+        ref = x.view(torch.bfloat16).double() @ w.view(torch.bfloat16).double().T
+        assert float((y.double() - ref).abs().max()) <= 2e-5 * float(ref.abs().max())
 
 
 def test_gemm_lm_head_large_window_sampled():
