@@ -475,6 +475,17 @@ int nightjar_gemm_with_plan(int32_t dtype, const void* x, const void* w, void* y
                             int32_t epilogue, int32_t kernel, int32_t split_k, void* workspace,
                             size_t workspace_bytes, void* stream);
 
+/*
+ * The plan that nightjar_gemm_with_plan runs for these arguments (NJ_GEMM_AUTO:
+ * that nightjar_gemm runs), for tests that mean a particular kernel.  info
+ * receives six values: the kernel (0 fp32, 1 weight-streaming, 2 LDS-tiled,
+ * 3 small-window), the x rows and the weight rows of a workgroup's tile, the K
+ * chunks that the most cut tile is summed from, the workgroups, and 1 for a
+ * stream-K schedule (tiles cut unevenly).  Host only.  Returns NJ_OK or NJ_EINVAL.
+ */
+int nightjar_gemm_plan_info(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t kernel,
+                            int32_t split_k, int32_t* info);
+
 #ifdef __cplusplus
 }
 #endif

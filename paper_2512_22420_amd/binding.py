@@ -94,6 +94,7 @@ _SIGS = {
     "nightjar_gemm_workspace_bytes": (_sz, [_i32, _i32, _i32, _i32, _i32]),
     "nightjar_gemm_with_plan": (ctypes.c_int, [_i32, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp, _sz,
                                                _vp]),
+    "nightjar_gemm_plan_info": (_i32, [_i32, _i32, _i32, _i32, _i32, _i32, _i32, ctypes.POINTER(_i32)]),
     "nightjar_gemm_plan_workspace_bytes": (_sz, [_i32, _i32, _i32, _i32, _i32, _i32, _i32]),
     "nightjar_accept_workspace_bytes": (_sz, [_i32, _i32, _i32]),
     "nightjar_rmsnorm_rope_workspace_bytes": (_sz, [ctypes.POINTER(ModelDesc), _i32, _i32]),
@@ -242,6 +243,14 @@ def gemm_plan_workspace_bytes(dtype, M, N, K, epilogue, kernel, split_k) -> int:
     if n == 0:
         raise NightjarError(NJ_EINVAL, last_error())
     return n
+
+
+def gemm_plan_info(dtype, M, N, K, epilogue, kernel, split_k) -> dict:
+    """The kernel, tile and split that gemm_with_plan (or, with NJ_GEMM_AUTO, gemm) runs."""
+    info = (_i32 * 6)()
+    _check(lib().nightjar_gemm_plan_info(dtype, M, N, K, epilogue, kernel, split_k, info))
+    return {"kernel": ("f32", "stream", "tile", "small")[info[0]], "tile": (info[1], info[2]), "chunks": info[3],
+            "workgroups": info[4], "stream_k": bool(info[5])}
 
 
 def gemm_with_plan(dtype, x, w, y, M, N, K, epilogue, kernel, split_k, workspace, workspace_nbytes,

@@ -984,6 +984,22 @@ size_t nightjar_gemm_plan_workspace_bytes(int32_t dtype, int32_t M, int32_t N, i
   return dtype == NJ_BF16 ? gemm_plan_bytes(p) : kAlign;
 }
 
+int nightjar_gemm_plan_info(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t kernel,
+                            int32_t split_k, int32_t* info) {
+  if (!info) return fail(NJ_EINVAL, "info is NULL");
+  GemmPlan p;
+  if (plan_with(dtype, M, N, K, epilogue & ~NJ_GEMM_KBLOCKED, kernel, split_k, &p) != NJ_OK) return NJ_EINVAL;
+  const bool tiled = p.tile != kTileNone, small = p.small != 0;
+  info[0] = dtype != NJ_BF16 ? 0 : tiled ? 2 : small ? 3 : 1;
+  info[1] = tiled ? tile_bm(p.tile) : 16 * p.mt;
+  info[2] = tiled ? tile_bn(p.tile) : small ? N / std::max(1, p.ntiles) : 128;
+  info[3] = p.nkc;
+  info[4] = tiled ? p.grid : p.ntiles * p.mblocks * p.nkc;
+  info[5] = tiled && !tile_one_segment(p, K) ? 1 : 0;
+  if (dtype != NJ_BF16) info[1] = info[2] = info[3] = info[4] = 0;
+  return NJ_OK;
+}
+
 int nightjar_gemm_with_plan(int32_t dtype, const void* x, const void* w, void* y, int32_t M, int32_t N, int32_t K,
                             int32_t epilogue, int32_t kernel, int32_t split_k, void* workspace,
                             size_t workspace_bytes, void* stream) {

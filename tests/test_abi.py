@@ -151,6 +151,24 @@ def test_gemm_without_split_needs_no_scratch(M, N, K, epi):
     assert nb.gemm_workspace_bytes(nb.NJ_BF16, M, N, K, epi) == 256
 
 
+def test_gemm_plan_info():
+    res = nb.NJ_GEMM_RESIDUAL
+    assert nb.gemm_plan_info(nb.NJ_F32, 4, 50, 70, res, nb.NJ_GEMM_AUTO, 0)["kernel"] == "f32"
+    small = nb.gemm_plan_info(nb.NJ_BF16, 8, 4096, 14336, res, nb.NJ_GEMM_AUTO, 0)
+    assert small == {"kernel": "small", "tile": (16, 16), "chunks": 1, "workgroups": 256, "stream_k": False}
+    stream = nb.gemm_plan_info(nb.NJ_BF16, 48, 4096, 14336, res, nb.NJ_GEMM_STREAM, 4)
+    assert stream == {"kernel": "stream", "tile": (48, 128), "chunks": 4, "workgroups": 128, "stream_k": False}
+    tile = nb.gemm_plan_info(nb.NJ_BF16, 768, 4096, 14336, res | nb.NJ_GEMM_KBLOCKED, nb.NJ_GEMM_TILE_128x256, -200)
+    assert tile["kernel"] == "tile" and tile["tile"] == (128, 256) and tile["stream_k"] and tile["workgroups"] == 198
+    for M in (160, 320, 600, 2048):  # the 320x256 tile runs whole sums only
+        for N, K in ((128256, 4096), (37888, 3584), (4096, 14336)):
+            p = nb.gemm_plan_info(nb.NJ_BF16, M, N, K, nb.NJ_GEMM_STORE, nb.NJ_GEMM_AUTO, 0)
+            assert p["tile"] != (320, 256) or (p["chunks"] == 1 and not p["stream_k"])
+    with pytest.raises(nb.NightjarError):
+        nb.gemm_plan_info(nb.NJ_BF16, 64, 256, 256, res, nb.NJ_GEMM_AUTO, 2)
+    assert nb.lib().nightjar_gemm_plan_info(nb.NJ_BF16, 64, 256, 256, res, nb.NJ_GEMM_AUTO, 0, None) == nb.NJ_EINVAL
+
+
 def test_stage_entries_reject_bad_arguments_on_host():
     desc = model_desc(W.QWEN7B)  # G = 7: k = 9 gives 70 query rows per KV head
     n = nb.attn_workspace_bytes(desc, 1, 9)

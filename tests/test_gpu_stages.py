@@ -91,6 +91,8 @@ def test_gemm_small_windows(M, N, K, epi):
     residual limit (4112)."""
     rng = np.random.default_rng(M * 31 + N + K)
     rows = 2 * N if epi == nb.NJ_GEMM_SWIGLU else N
+    small = M <= 16 and (epi == nb.NJ_GEMM_SWIGLU or N <= 4096)
+    assert nb.gemm_plan_info(nb.NJ_BF16, M, rows, K, epi, nb.NJ_GEMM_AUTO, 0)["kernel"] == ("small" if small else "stream")
     x = W.f32_to_bf16_bits(rng.standard_normal((M, K), dtype=np.float32))
     w = W.f32_to_bf16_bits(rng.standard_normal((rows, K), dtype=np.float32) * 0.03)
     y0 = rng.standard_normal((M, N), dtype=np.float32)
@@ -248,25 +250,29 @@ def test_gemm_kblocked_operands_match_row_major(kernel, split, M, N, K, epi):
                           epi | nb.NJ_GEMM_KBLOCKED, nb.NJ_GEMM_STREAM, 0, ws.data_ptr(), nbytes, _stream())
 
 
-@pytest.mark.parametrize("kernel,M,N,K,epi", [
-    (nb.NJ_GEMM_AUTO, 150, 2 * 14336, 512, nb.NJ_GEMM_SWIGLU),       # 160x128, one ragged row of tiles
-    (nb.NJ_GEMM_AUTO, 160, 28672, 512, nb.NJ_GEMM_STORE),            # 160x128, full
-    (nb.NJ_GEMM_AUTO, 150, 4096, 14336, nb.NJ_GEMM_RESIDUAL),        # 160x128, split K
-    (nb.NJ_GEMM_AUTO, 310, 256 * 200 + 16, 192, nb.NJ_GEMM_STORE),   # 320x256, ragged both ways, 6 stages
-    (nb.NJ_GEMM_AUTO, 320, 2 * 128 * 220, 64, nb.NJ_GEMM_SWIGLU),    # 320x256, fewer stages than buffers
-    (nb.NJ_GEMM_AUTO, 257, 256 * 210, 320, nb.NJ_GEMM_RESIDUAL),     # 320x256, 10 stages
-    (nb.NJ_GEMM_AUTO, 190, 2 * 14336, 512, nb.NJ_GEMM_SWIGLU),       # 192x128, ragged
-    (nb.NJ_GEMM_AUTO, 192, 28672 - 16, 512, nb.NJ_GEMM_STORE),       # 192x128, ragged columns
-    (nb.NJ_GEMM_TILE_128x128, 257, 128 * 85, 128, nb.NJ_GEMM_STORE),  # 255 workgroups: 8 waves, fewer stages than buffers
-    (nb.NJ_GEMM_TILE_128x128, 257, 128 * 86, 128, nb.NJ_GEMM_STORE),  # 258: 4 waves, two workgroups per CU
-    (nb.NJ_GEMM_TILE_96x128, 193, 128 * 85, 64, nb.NJ_GEMM_RESIDUAL),  # 255, several M tiles: 8 stage buffers
-    (nb.NJ_GEMM_TILE_96x128, 193, 128 * 86, 64, nb.NJ_GEMM_RESIDUAL),  # 258: 4
-    (nb.NJ_GEMM_TILE_96x128, 90, 128 * 40 - 48, 448, nb.NJ_GEMM_STORE),  # one M tile: 4
+@pytest.mark.parametrize("kernel,M,N,K,epi,tile", [
+    (nb.NJ_GEMM_AUTO, 150, 2 * 14336, 512, nb.NJ_GEMM_SWIGLU, (160, 128)),       # one ragged row of tiles
+    (nb.NJ_GEMM_AUTO, 160, 28672, 512, nb.NJ_GEMM_STORE, (160, 128)),            # full
+    (nb.NJ_GEMM_AUTO, 150, 4096, 14336, nb.NJ_GEMM_RESIDUAL, (160, 128)),        # split K
+    (nb.NJ_GEMM_AUTO, 310, 256 * 200 + 16, 192, nb.NJ_GEMM_STORE, (320, 256)),   # ragged both ways, 6 stages
+    (nb.NJ_GEMM_AUTO, 320, 2 * 128 * 220, 64, nb.NJ_GEMM_SWIGLU, (320, 256)),    # fewer stages than buffers
+    (nb.NJ_GEMM_AUTO, 257, 256 * 210, 320, nb.NJ_GEMM_RESIDUAL, (320, 256)),     # 10 stages
+    (nb.NJ_GEMM_AUTO, 190, 2 * 14336, 512, nb.NJ_GEMM_SWIGLU, (192, 128)),       # ragged
+    (nb.NJ_GEMM_AUTO, 192, 28672 - 16, 512, nb.NJ_GEMM_STORE, (192, 128)),       # ragged columns
+    (nb.NJ_GEMM_AUTO, 180, 4096, 14336, nb.NJ_GEMM_RESIDUAL, (192, 128)),        # split K
+    (nb.NJ_GEMM_TILE_128x128, 257, 128 * 85, 128, nb.NJ_GEMM_STORE, (128, 128)),  # 255 workgroups: 8 waves, fewer stages than buffers
+    (nb.NJ_GEMM_TILE_128x128, 257, 128 * 86, 128, nb.NJ_GEMM_STORE, (128, 128)),  # 258: 4 waves, two workgroups per CU
+    (nb.NJ_GEMM_TILE_96x128, 193, 128 * 85, 64, nb.NJ_GEMM_RESIDUAL, (96, 128)),  # 255, several M tiles: 8 stage buffers
+    (nb.NJ_GEMM_TILE_96x128, 193, 128 * 86, 64, nb.NJ_GEMM_RESIDUAL, (96, 128)),  # 258: 4
+    (nb.NJ_GEMM_TILE_96x128, 90, 128 * 40 - 48, 448, nb.NJ_GEMM_STORE, (96, 128)),  # one M tile: 4
 ])
-def test_gemm_small_tile_shapes(kernel, M, N, K, epi):
+def test_gemm_small_tile_shapes(kernel, M, N, K, epi, tile):
     """The tile shapes and buffer depths of windows of up to ~600 rows, at the
     edges of their rules, row-major and k-blocked x: the same bytes, within
     the tolerance of the reference."""
+    plan = nb.gemm_plan_info(nb.NJ_BF16, M, N, K, epi, kernel, 0)
+    assert plan["kernel"] == "tile" and plan["tile"] == tile and not plan["stream_k"], plan
+    assert (plan["chunks"] > 1) == (K == 14336)
     x, w, y0 = _gemm_case(M, N, K, epi, seed=M + N + K + kernel)
     Nout = N // 2 if epi == nb.NJ_GEMM_SWIGLU else N
     dw = _devw(w)
@@ -293,6 +299,31 @@ def test_gemm_small_tile_shapes(kernel, M, N, K, epi):
     ref = _gemm_ref(x, w, epi, y0)
     assert np.abs(_gemm_out(torch.from_numpy(outs[0]), epi) - ref).max() <= _gemm_tol(ref, epi)
     assert nb.device_error(ws.data_ptr(), nbytes, _stream()) == 0
+
+
+@pytest.mark.parametrize("M,N,K,epi,tile", [
+    (129, 16464, 5184, nb.NJ_GEMM_STORE, (160, 128)),
+    (129, 2 * 8304, 5888, nb.NJ_GEMM_SWIGLU, (160, 128)),
+    (170, 16768, 6656, nb.NJ_GEMM_RESIDUAL, (192, 128)),
+])
+def test_gemm_stream_k_of_the_8_stage_tiles(M, N, K, epi, tile):
+    """The stream-K schedules that the planner picks for one row of 160x128 or
+    192x128 tiles with a few more tiles than CUs."""
+    plan = nb.gemm_plan_info(nb.NJ_BF16, M, N, K, epi, nb.NJ_GEMM_AUTO, 0)
+    assert plan["tile"] == tile and plan["stream_k"], plan
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N)
+    x, w = W.device_normal_bf16(gen, (M, K), 1.0), W.device_normal_bf16(gen, (N, K), 0.03)
+    ref = x.view(torch.bfloat16).double() @ w.view(torch.bfloat16).double().T
+    if epi == nb.NJ_GEMM_SWIGLU:
+        ref = torch.nn.functional.silu(ref[:, : N // 2]) * ref[:, N // 2:]
+        y = torch.empty(ref.shape, dtype=torch.int16, device="cuda")
+    else:
+        y = torch.randn(ref.shape, generator=gen, device="cuda") if epi == nb.NJ_GEMM_RESIDUAL else torch.empty(ref.shape, device="cuda")
+        ref += y.double() if epi == nb.NJ_GEMM_RESIDUAL else 0
+    _gemm(nb.NJ_BF16, x, pack_weight(w), y, M, N, K, epi)
+    got = y.view(torch.bfloat16).double() if epi == nb.NJ_GEMM_SWIGLU else y.double()
+    assert float((got - ref).abs().max()) <= _gemm_tol(ref.cpu().numpy(), epi)
 
 
 @pytest.mark.parametrize("M,N,K,epi", [
