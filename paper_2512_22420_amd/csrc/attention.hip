@@ -240,9 +240,11 @@ __global__ __launch_bounds__(256, 2) void attn_reg_kernel(AttnK a) {
   const int n = npw > wave ? (npw - wave + NP - 1) / NP : 0;  // this wave's
 
   // Page ids of 32 of the wave's pairs: lane l holds block l & 1 of pair
-  // idbase + l / 2.  kNoBlock: no such block (or a bad id: any table entry
-  // outside [0, num_blocks) of a block inside the context, -1 included): the
-  // window block's memory is read in its place, and masked out.
+  // idbase + l / 2.  kNoBlock: the window block's memory is read in its place.
+  // Past the split's last block that is masked out, with the pair's tokens past
+  // the context; for a bad id (any table entry outside [0, num_blocks) of a
+  // block inside the context, -1 included) it is not: the window's keys then
+  // count as the block's, and the output is invalid, as kErrBlock says.
   constexpr int kNoBlock = INT_MIN;
   int idv = kNoBlock, idbase = 0;
   bool bad = false;
@@ -478,10 +480,11 @@ __global__ __launch_bounds__(256, 2) void attn_lds_kernel(AttnK a) {
   // This wave's piece of a pair: block second of it, K (waves 0, 1) or V (2, 3)
   const int second = wave & 1;
   const bool is_v = wave >= 2;
-  // Page ids of its block of 64 pairs, pair idbase + lane; kNoBlock (no such
-  // block, or a bad id: any table entry outside [0, num_blocks) of a block
-  // inside the context, -1 included): the window block's memory is read
-  // instead, and masked out.
+  // Page ids of its block of 64 pairs, pair idbase + lane.  kNoBlock: the window
+  // block's memory is read instead.  Past the split's last block that is masked
+  // out; for a bad id (any table entry outside [0, num_blocks) of a block inside
+  // the context, -1 included) it is not, and the output is invalid, as kErrBlock
+  // says.
   constexpr int kNoBlock = INT_MIN;
   int idv = kNoBlock, idbase = 0;
   bool bad = false;
@@ -812,12 +815,19 @@ hipError_t launch_attention(const AttnArgs& x, hipStream_t s) {
           (int)std::min<size_t>(attention_partial_floats(x.B, x.Hkv, x.T, G, kD) / (kD + 2) * 2 * 4, INT32_MAX),
           x.out_kblocked ? x.B * x.T : 0};
   if (!x.work || x.wgs < x.B * x.Hkv || x.wgs > x.B * x.Hkv + kExtraWorkgroups) return hipErrorInvalidValue;
-  // A cache read that the last-level cache (256 MB) cannot keep to the next
-  // launch anyway goes non-temporal, which reads faster from HBM (64 sequences of
-  // 4096 tokens 185 -> 165 us, of ~870 tokens 50.3 -> 47.8; 7B shape at 56 rows
-  // 269 -> 248); a small one stays cacheable (8 sequences of 1024 tokens 14.0
-  // against 15.0 us when they come round again).  The host knows the largest
-  // context the table allows, not the contexts.
+  // A cache read that does not stay in the last-level cache (256 MB) until the
+  // layer comes round again goes non-temporal, which reads faster from HBM.
+  // Measured with plain -> streaming loads (us; tables as wide as the contexts,
+  // caches from HBM): 8B at 250 MB 56.1 -> 51.5, at 190 MB 47.7 -> 46.4, at 130
+  // MB 44.0 -> 45.1; 7B with 56 rows at 360 MB 83.0 -> 73.7, at 140 MB 57.4 ->
+  // 54.5, at 95 MB 52.3 -> 49.9, at 48 MB 33.5 -> 33.2; 1B at 255 MB 62.1 ->
+  // 59.1, at 128 MB 42.3 -> 42.6: the line of 128 MB lies where they cross, by
+  // 2-5% earlier or later by shape.  A cache of up to 220 MB that is still in the
+  // last-level cache loses up to 15% (8B at 160 MB 38.1 -> 44.0), but a model's
+  // other layers and weights come between.  The host knows the contexts that the
+  // table allows, not the contexts: in a wider table a small read streams too,
+  // which costs up to 5% (32 MB 20.0 -> 20.0, 10 MB 15.9 -> 16.2, 96 MB 38.4 ->
+  // 40.1).
   const bool stream = (size_t)x.B * x.max_blocks * x.Hkv * (2 * kBlock * kD * 2) > kStreamBytes;
   const dim3 grid(x.wgs), block(256);
   if (RT == 1) {

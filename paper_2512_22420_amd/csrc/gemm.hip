@@ -1088,8 +1088,13 @@ namespace {
 // - residual GEMMs (O, down) of one row tile: 8B 12.0 -> 8.0 and 23.2 -> 20.3,
 //   7B 15.3 -> 7.4 and 26.8 -> 24.9, 1B 10.4 -> 4.8 and 12.8 -> 10.5.  Each
 //   workgroup reads all of x for its 16 columns, so at two row tiles it only
-//   pays with k-blocked x (the step's, kEpiResidualNorm) and up to 4096 k (8B O
-//   13.7 -> 10.7; 8B down 25 -> 29);
+//   pays with k-blocked x (the step's, kEpiResidualNorm) and few k.  17, 24 and
+//   32 rows of 4096 columns: K = 2048 11.4, 11.9, 12.2 -> 7.3, 7.3, 7.3, K = 4096
+//   12.0, 12.3, 12.6 -> 9.3, 9.9, 10.7, K = 6144 15.3, 15.7, 16.0 -> 12.1, 13.0,
+//   14.5, K = 8192 16.5, 16.7, 16.9 -> 17.2, 17.8, 18.9, K = 14336 23.6, 23.8,
+//   23.9 -> 24.1, 26.1, 29.0; 2048 columns, K = 8192 13.0, 13.2, 13.5 -> 13.8,
+//   15.0, 16.7.  The line is at 4096; no shape measured lies between there and
+//   6144, where it would still pay;
 // - QKV with RoPE: 8B 14.1 -> 12.0 and, two row tiles, 15.9 -> 14.9 (three: 17.7
 //   -> 18.4), 7B 16.3 -> 10.0, 1B 11.5 -> 7.8;
 // - gate/up of one row tile (two: 8B 37 -> 48), unless the streaming kernel
@@ -1121,7 +1126,9 @@ GemmPlan gemm_plan_uncached(int M, int N, int K, int epi) {
     p.mt = (M + 15) / 16;
     p.ntiles = epi == kEpiQkvRope ? N / 32 : epi == kEpiSwiglu ? N / 32 : N / 16;
     p.mblocks = p.nkc = p.depth = 1;
-    // 16 waves where fewer workgroups than CUs have long sums (8B QKV at 16 rows 12.8 -> 12.1 us; else no gain)
+    // 16 waves where fewer workgroups than CUs have long sums: 4 to 32 rows of 3072 to 7168 columns (QKV), K = 4096 to
+    // 6144, up to 2.5% faster and at most 1% slower (6144 x 4096: 11.7, 12.6, 13.9, 14.6 -> 11.6, 12.6, 13.5, 14.6 us
+    // at 4, 16, 24, 32 rows); at K = 2048 and 3584 4-9% slower (6144 x 2048, 16 rows: 8.5 -> 8.9)
     p.nw = epi == kEpiQkvRope && p.ntiles < 256 && K >= 4096 ? 16 : 8;
     return p;
   }

@@ -129,17 +129,18 @@ hipError_t launch_gemm_logits(const void* x, const void* w, float* y, float* sta
                               int* counters, float* part, hipStream_t s, bool* stats_written, bool x_kblocked = false);
 // RMSNorm folded into the weight-streaming GEMMs.  A producer (residual
 // epilogue kEpiResidualNorm) adds into h and writes xg = bf16(h * gain) and
-// ssq_out[m][t], the sum of h^2 over output columns 128t .. 128t+127; a
+// ssq_out[m][t], the sum of h^2 over output columns 128t .. 128t+127 (16t ..
+// 16t+15 from the small-window kernel); a
 // consumer (x = xg) scales row m of its product by
 // 1 / sqrt(sum_t ssq_in[m][t] / K + eps) before its epilogue.  stats: the
 // kEpiLogits chunk statistics.
 struct GemmNorm {
   const float* ssq_in;  // consumer side (nullable)
-  int nt_in;            // partials per row (<= 64)
+  int nt_in;            // partials per row: up to 64 (128 columns each), or kMaxSsqSegments at windows of the small-window kernel
   float eps;
   const void* gain;     // producer side: bf16 [N]
   void* xg;             // bf16 [M][N], or k-blocked [N/32][M][32] with xg_kb
-  float* ssq_out;       // [M][ceil(N / 128)]
+  float* ssq_out;       // [M][gemm_ssq_segments(M, N, K)]
   float* stats;         // kEpiLogits only
   int xg_kb = 0;
 };
