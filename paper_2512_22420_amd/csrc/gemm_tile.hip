@@ -43,18 +43,24 @@ __device__ __forceinline__ float silu_mul(float gte, float up) { return gte / (1
 constexpr float kLog2e = 1.4426950408889634f;
 
 // An x unit in LDS: its 16 rows of 64 bytes, the four 16-byte pieces of row r
-// (k 8 j .. 8 j + 7) at positions j ^ x_swizzle(r), so that the 16 rows' pieces
-// j, as a fragment read takes them, lie in different banks (any 8 consecutive
-// rows too).  Four consecutive lanes load one row's 64 bytes, and the L1 looks
-// its line up once for them.  In operand order (lanes 0..15 the 16 rows) a
-// row-major unit took 64 lookups and a k-blocked one 32 where 16 do, and the
-// kernel waited for the L1's lookups: 8B gate/up at 160 rows, row-major x, 24.0
-// -> 9.3 million lookups and 57.3 -> 44.8 us with the weights in the last-level
-// cache, 73.4 -> 66.7 from HBM (k-blocked 13.9 -> 9.1 million, 42.9 -> 41.9);
-// 7B at 2048 rows 186 -> 80 million, 497 -> 445 us (110 -> 75, 435 -> 425).
-// Row-major x stays behind k-blocked x: a stage takes half of each row's
-// 128-byte line, and the other half is asked for while the first is on its way.
-__device__ __forceinline__ int x_swizzle(int r) { return (((r >> 1) ^ (r >> 3)) & 1) | ((r >> 1) & 2); }
+// (k 8 j .. 8 j + 7) at positions j ^ x_swizzle(r).  A 16-byte fragment read
+// serves lanes 0-3, 12-15, 20-27 together, then 4-11, 16-19, 28-31, and the same
+// from 32 on: these are rows 0-3 and 12-15 of one piece with rows 4-11 of the
+// next, or the other way round, and the swizzle 0, 2, 3, 1 of the row quads puts
+// their 16 pieces in different banks (SQ_LDS_BANK_CONFLICT 0).  Four consecutive
+// lanes load one row's 64 bytes, and the L1 looks its line up once for them.  In
+// operand order (lanes 0..15 the 16 rows) a row-major unit took 64 lookups and a
+// k-blocked one 32 where 16 do, and the kernel waited for the L1's lookups: 8B
+// gate/up at 160 rows, row-major x, 24.0 -> 9.3 million lookups and 57.3 -> 44.7
+// us with the weights in the last-level cache, 73.4 -> 66.7 from HBM (k-blocked
+// 13.9 -> 9.1 million, 42.9 -> 40.2); 7B at 2048 rows 186 -> 80 million, 497 ->
+// 437 us (110 -> 75, 435 -> 413).  Row-major x stays behind k-blocked x: a stage
+// takes half of each row's 128-byte line, and the other half is asked for while
+// the first is on its way.
+__device__ __forceinline__ int x_swizzle(int r) {
+  const int q = r >> 2;
+  return ((q << 1) ^ (q >> 1) * 3) & 3;
+}
 
 struct TileK {
   const bf16_t* X;
