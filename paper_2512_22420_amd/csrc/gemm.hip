@@ -1087,8 +1087,15 @@ namespace {
 // kernels measured, us, streaming -> small; 8B, 7B and 1B layer shapes):
 // - residual GEMMs (O, down) of one row tile: 8B 12.0 -> 8.0 and 23.2 -> 20.3,
 //   7B 15.3 -> 7.4 and 26.8 -> 24.9, 1B 10.4 -> 4.8 and 12.8 -> 10.5.  Each
-//   workgroup reads all of x for its 16 columns, so at two row tiles it only
-//   pays with k-blocked x (the step's, kEpiResidualNorm) and few k.  17, 24 and
+//   workgroup reads all of x for its 16 columns.  With row-major x (callers of
+//   nightjar_gemm) that costs more than it saves from 10 rows on where K is
+//   long; 8, 10 and 16 rows of 4096 columns: K = 4096 12.2, 12.2, 12.5 -> 8.9,
+//   9.3, 10.7, K = 6144 15.5, 15.5, 14.7 -> 11.5, 12.1, 12.9, K = 8192 16.1,
+//   15.7, 15.9 -> 16.1, 16.6, 17.6, K = 14336 23.6, 22.8, 22.9 -> 22.5, 23.4,
+//   25.4 (up to 27.7); 2048 columns, K = 8192 11.8, 11.9, 12.1 -> 11.6, 12.3,
+//   14.3; 3584 columns, K = 18944 26.6, 26.7, 27.2 -> 25.6, 26.9, 31.5.  At two
+//   row tiles it only pays with k-blocked x (the step's, kEpiResidualNorm) and
+//   few k.  17, 24 and
 //   32 rows of 4096 columns: K = 2048 11.4, 11.9, 12.2 -> 7.3, 7.3, 7.3, K = 4096
 //   12.0, 12.3, 12.6 -> 9.3, 9.9, 10.7, K = 6144 15.3, 15.7, 16.0 -> 12.1, 13.0,
 //   14.5, K = 8192 16.5, 16.7, 16.9 -> 17.2, 17.8, 18.9, K = 14336 23.6, 23.8,
@@ -1105,7 +1112,7 @@ bool small_wins(int M, int N, int K, int epi) {
   const int mt = (M + 15) / 16;
   if (mt > kSmallMaxTiles || K % 32) return false;
   switch (epi) {
-    case kEpiResidual: return N / 16 <= kMaxSsqSegments && mt == 1;
+    case kEpiResidual: return N / 16 <= kMaxSsqSegments && mt == 1 && (M <= 8 || K <= 6144);
     case kEpiResidualNorm: return N / 16 <= kMaxSsqSegments && (mt == 1 || K <= 4096);
     case kEpiQkvRope: return N % 128 == 0 && mt <= 2;
     case kEpiSwiglu: {

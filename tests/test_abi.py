@@ -169,6 +169,14 @@ def test_gemm_plan_info():
     assert nb.lib().nightjar_gemm_plan_info(nb.NJ_BF16, 64, 256, 256, res, nb.NJ_GEMM_AUTO, 0, None) == nb.NJ_EINVAL
 
 
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (8, 4096, 14336, "small"), (9, 4096, 14336, "stream"), (16, 3584, 18944, "stream"), (16, 2048, 8192, "stream"),
+    (16, 4096, 6144, "small"), (9, 4096, 6176, "stream")])
+def test_row_major_residual_of_long_k_streams_past_8_rows(M, N, K, kernel):
+    """There the small-window kernel's reads of row-major x cost more than its K split saves."""
+    assert nb.gemm_plan_info(nb.NJ_BF16, M, N, K, nb.NJ_GEMM_RESIDUAL, nb.NJ_GEMM_AUTO, 0)["kernel"] == kernel
+
+
 def test_stage_entries_reject_bad_arguments_on_host():
     desc = model_desc(W.QWEN7B)  # G = 7: k = 9 gives 70 query rows per KV head
     n = nb.attn_workspace_bytes(desc, 1, 9)
