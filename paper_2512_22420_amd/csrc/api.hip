@@ -895,9 +895,10 @@ int nightjar_pack_weight(const void* src, void* dst, int32_t N, int32_t K, void*
 }
 
 // A GEMM workspace: [device error word][counters][partials]; a plan that does
-// not split K uses none of it but the error word.  A split plan's partials lie past the counters that any plan may have, not only
-// its own, so that calls of other shapes on the same workspace find their
-// counters as they left them (zero).
+// not split K uses none of it but the error word.  A split plan's partials lie
+// past the counters that any plan may have, not only its own, so that calls of
+// other shapes on the same workspace find their counters as they left them
+// (zero).
 static size_t gemm_part_offset(const GemmPlan& p) { return p.part_bytes ? kAlign + kGemmCounterBytes : kAlign; }
 static size_t gemm_plan_bytes(const GemmPlan& p) { return gemm_part_offset(p) + p.part_bytes; }
 

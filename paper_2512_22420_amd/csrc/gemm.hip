@@ -986,10 +986,14 @@ namespace {
 // the plan chosen is the fastest measured one, or within 3% of it, at 70 of
 // 83 points and within 15% at the others (the sustained fractions below are
 // fitted for ranking plans, so they sit above the measured ones).  The 160x128
-// and 192x128 shapes and the 8-wave 128x128 one, added later, were fitted to
-// the same GEMMs at 65..384 rows (us, without -> with them): 8B gate/up 112
-// rows 56 -> 51, 160 rows 63 -> 60, 8B down 112 rows 39 -> 34, 144 rows 43 ->
-// 39.5, 7B down 144 rows 51 -> 46.6, 8B QKV 160 rows 27.9 -> 26.6.
+// and 192x128 shapes and the 8-wave 128x128 one were fitted to the same GEMMs
+// at 65..384 rows.  k-blocked x, us, fastest of the other shapes -> the one
+// picked: 8B gate/up 112 rows 53.7 -> 49.4, 160 rows 58.1 -> 53.9, 192 rows 61.3
+// -> 57.3, 8B down 112 rows 36.8 -> 33.0, 144 rows 36.9 -> 36.5, 160 rows 37.9 ->
+// 36.4, 180 rows 40.1 -> 40.6, 7B down 144 rows 43.4 -> 42.4, 8B QKV 160 rows 27.0
+// -> 25.9.  Row-major x gets the same plans; its loads cost more where the tile
+// is narrow (8B gate/up 160 rows 62.5 -> 65.6, 192 rows 67.8 -> 75.6, down 180
+// rows 42.3 -> 49.3).
 // Tiled kernel: rounds of resident workgroups times one tile's MFMA time at
 // the tile shape's sustained fraction of peak, plus, when tiles are cut, the
 // last arriver's reduction (one CU reads nkc partial tiles) and the partial

@@ -197,10 +197,13 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_tile_kernel(TileK a) {
   constexpr int XU = BM / 16, WU = BN / 16;        // 1 KB units per stage
   // units each wave loads per stage: wave w takes units w, w + NW, ...; when
   // they do not split evenly, the first REM waves load one more than the
-  // others (the load-counter waits below count each wave's own).  Before, the
-  // surplus slots loaded the last unit again, up to a third more loads: 8B
-  // gate/up 160 rows 60.1 -> 56.9 us, 320 rows split down 55.6 -> 52.0.  The
-  // 320-row tile keeps those (LM head 320 rows 294 -> 304 without them).
+  // others (the load-counter waits below count each wave's own).  Surplus slots
+  // that load the last unit again are up to a third more loads; without them,
+  // us, k-blocked x (row-major): 8B gate/up 160 rows 57.4 -> 54.6 (71.2 -> 67.7),
+  // 192 rows 59.1 -> 57.2 (78.1 -> 75.8), QKV 384 rows 38.6 -> 37.5, 305 rows
+  // gate/up 76.4 -> 76.9 (89.5 -> 85.6) and split down 54.1 -> 53.3 (59.0 -> 57.4).
+  // The 320-row tile keeps them: LM head 320 rows 298.1, without 301.6 (row-major
+  // 323.9, 316.3), 600 rows 529, 535 (550, 554).
   constexpr int UPW = (XU + WU + NW - 1) / NW, REM = TM > 8 ? 0 : (XU + WU) % NW;
   constexpr int STAGE = (XU + WU) * 512;           // bf16 elements per stage buffer
   constexpr int DIST = NBUF - 1;                   // stages in flight ahead of the one multiplied
@@ -741,11 +744,13 @@ hipError_t launch_gemm_tile(const void* x, const void* w, void* y, int M, int N,
       if (!one_segment) return hipErrorInvalidValue;
       return launch_shape<256, 256, 2, 4, 4, false>(a, epi, s);
     // 8 waves of 160 x 64 (x fragments through a ring, no second set): a tile
-    // multiplies 142 times per byte it loads (160 x 256: 98), and what holds
-    // these loops back is bytes through the CU's L1.  Whole sums only.  LM head
-    // of the 8B shape at 305 rows 345 -> 294 us (76% of the rate a large
-    // library product reaches), 600 rows 605 -> 535, 7B gate/up 305 rows
-    // 106 -> 98, 8B gate/up 600 rows 140 -> 120
+    // multiplies 142 times per byte it loads (160 x 256: 98), and these loops
+    // wait for their loads (8B LM head at 305 rows, 160 x 256: addressers busy
+    // 82% of the time, L1s waiting for misses 55%, matrix pipes busy 46%; 320 x
+    // 256: 74%, 61%, 58%).  Whole sums only.  Fastest of the other shapes ->
+    // this one, us, k-blocked x: 8B LM head 305 rows 333 -> 298 (75% of the rate
+    // a large library product reaches), 600 rows 607 -> 534, 7B gate/up 305 rows
+    // 122 -> 96, 8B gate/up 600 rows 137 -> 124
     case kTile320x256:
       if (!one_segment || split) return hipErrorInvalidValue;
       return launch_shape<320, 256, 2, 4, 4, false>(a, epi, s);
@@ -757,21 +762,22 @@ hipError_t launch_gemm_tile(const void* x, const void* w, void* y, int M, int N,
     // weight matrix has few rows
     case kTile96x256: return launch_shape_any<96, 256, 2, 4, 4>(a, epi, one_segment, s);
     // several M tiles on up to one workgroup per CU: twice the stages in flight
-    // instead of room for a second workgroup (8B O 305 rows 28.3 -> 26.4 us, 600
-    // rows 37.6 -> 33.2, 7B QKV 512 rows 32.5 -> 28.5; with one M tile the
-    // longer prologue costs 2%: 8B QKV 80 rows 19.9 -> 20.4)
+    // instead of room for a second workgroup (8B O 600 rows 36.1 -> 31.9 us, 7B
+    // QKV 512 rows 31.2 -> 27.6).  With one M tile they give 2% (8B QKV 80 rows
+    // 20.0 -> 19.6, gate/up 70 rows 46.1 -> 45.3, 80 rows 47.4 -> 46.5) and are
+    // not taken
     case kTile96x128:
       if (p.grid <= 256 && p.mblocks > 1) return launch_shape_any<96, 128, 2, 4, 8>(a, epi, one_segment, s);
       return launch_shape_any<96, 128, 2, 4, 4>(a, epi, one_segment, s);
     // 8 waves of 80 x 32 and 96 x 32: windows of 129..192 rows in one row of
-    // tiles, weights read once (8B gate/up 160 rows 64.5 -> 60.2 us, 192 rows
-    // 73.3 -> 61.7..64.3; down 160 rows 53.5 -> 42.2)
+    // tiles, weights read once (fastest of the others -> these, us: 8B gate/up
+    // 160 rows 58.1 -> 53.9, 192 rows 61.3 -> 57.3; down 160 rows 37.9 -> 36.4)
     case kTile160x128: return launch_shape_any<160, 128, 2, 4, 8>(a, epi, one_segment, s);
     case kTile192x128: return launch_shape_any<192, 128, 2, 4, 6>(a, epi, one_segment, s);
     case kTile128x256: return launch_shape_any<128, 256, 2, 4, 4>(a, epi, one_segment, s);
     // up to one workgroup per CU: 8 waves and 8 stages (8B gate/up 80 rows
-    // 50.4 -> 47.3 us, 7B down 256 rows split in 4 61.7 -> 58.8); more: two
-    // resident workgroups of 4 waves (8B gate/up 256 rows 90 against 85)
+    // 47.0 -> 45.6 us, 7B down 256 rows split in 4 60.0 -> 58.5); more: two
+    // resident workgroups of 4 waves (8B gate/up 256 rows 87.2 against 81.5)
     default:
       if (p.grid <= 256) return launch_shape_any<128, 128, 2, 4, 8>(a, epi, one_segment, s);
       return launch_shape_any<128, 128, 2, 2, 4>(a, epi, one_segment, s);
