@@ -167,7 +167,7 @@ __device__ __forceinline__ float row_max(float v) {
 // max, so the token that leads a peaked row has a probability of exactly 1 in
 // bf16; a reference that lags the max saves rescales (7B shape, 256 sequences:
 // 247 us against 250, nothing at the other shapes) but rounds that token too
-// (8B step: error of the logits 0.0055 against 0.0052).  The accumulators are
+// (8B step of 61 sequences: error of the logits 0.0055 against 0.0053).  The accumulators are
 // rescaled under a uniform branch, only when a row's max rose.
 __device__ __forceinline__ bf16x8 softmax_step(const float (&st)[8], float scale, float& m_run, float& l_run, f32x4 (&o)[8]) {
   float bm = fmaxf(fmaxf(fmaxf(st[0], st[1]), fmaxf(st[2], st[3])), fmaxf(fmaxf(st[4], st[5]), fmaxf(st[6], st[7])));
